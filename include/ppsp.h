@@ -549,6 +549,9 @@ int ppsp_last_stats(ppsp_graph g, ppsp_stats *stats);
  *                     3: infinite (every frontier entry is extracted each round: the
  *                     Bellman-Ford instance of the stepping framework)
  *   "use_graph"       1: replay rounds through a captured hipGraph
+ *   "resident"        1 (default): independent queries on graphs of small degree (roads, grids)
+ *                     run one workgroup per query, from its roots to its end, where that is the
+ *                     faster way and no option that shapes rounds is set; 0: always in rounds
  *   "timeout_ms"      host-side limit on one wave's round loop (0 = none)
  *   "queue_cap"       frontier queue capacity in entries (grows x4, with a rerun of
  *                     the wave, whenever a round overflows it)

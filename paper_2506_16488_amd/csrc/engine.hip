@@ -34,6 +34,7 @@
 #include "../../include/ppsp.h"
 #include "mlp_dev.h"
 #include "ppsp_dev.h"
+#include "resident.h"
 
 namespace ppsp {
 hipError_t launch_init(const RoundArgs &A, hipStream_t st);
@@ -42,6 +43,7 @@ hipError_t launch_round(const RoundArgs &A, uint32_t grid, hipStream_t st, hipEv
 hipError_t launch_control(const RoundArgs &A, hipStream_t st);
 hipError_t launch_heavy(const RoundArgs &A, uint32_t grid, hipStream_t st, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
+hipError_t launch_resident(const ResidentArgs &A, bool pair, bool heur, bool rev, int threads, hipStream_t st);
 hipError_t launch_admit(const RoundArgs &A, const uint32_t *ids, uint32_t k, hipStream_t st);
 hipError_t launch_idle(const RoundArgs &A, hipStream_t st);
 hipError_t launch_mlp_forward(const float *P, const float *X, uint32_t n, float *logits, hipStream_t st);
@@ -257,6 +259,11 @@ struct ppsp_graph_s {
     // learned schedule
     DevBuf sc, bin, bin_after, sw_round, done_round, tot_arcs, tot_ent, trace, trace_s, trace_r, trace_b, trace_n, mlpw;
     // dense frontiers (options "dense_min" / "dense_force")
+    // resident searches (resident.hip): packed descriptors, results, frontier spill
+    DevBuf rin, rout, rspill;
+    int64_t opt_resident = 1;
+    bool compact = false;           // small degrees and frontiers (see ball_is_deep)
+    uint64_t clock_khz = 100000;    // wall_clock64() ticks per millisecond
     DevBuf dbits, dmode, dbase, dW, dread, docc, dlist, dcount;
     bool mlp_loaded = false;
     bool ml_plain = false;          // the fit's referee preferred the plain fixed path: LEARNED runs it
@@ -440,8 +447,11 @@ int ensure_events(ppsp_graph g, size_t k) {
     return PPSP_OK;
 }
 
+bool is_astar_kind(uint32_t kind) { return kind == K_ASTAR || kind == K_BIDA_F || kind == K_BIDA_B; }
+
 struct WaveOut {
     std::vector<uint64_t> mu;       // per pair slot
+    bool d32 = false;               // the searches' distances are 32-bit words (resident searches)
     std::vector<uint32_t> path;     // concatenated paths (if requested)
     std::vector<uint64_t> path_off; // npair + 1
     unsigned long long stats[ST_N] = {0};
@@ -456,8 +466,31 @@ struct WaveOut {
     uint64_t rows_total = 0;
 };
 
-// Runs one wave of searches to completion.
-int run_wave(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
+// Path lengths, then the paths of every pair slot of the wave's searches.
+int read_paths(ppsp_graph g, const RoundArgs &A, const PairDesc *pd, uint32_t npair, WaveOut &out) {
+    hipStream_t st = g->st;
+    CHK(ensure(g->pathlen, npair * 4));
+    CHK(ensure(g->pathoff, (npair + 1) * 8));
+    HIPCHK(launch_path_len(A, pd, g->pathlen.as<uint32_t>(), st));
+    std::vector<uint32_t> len(npair);
+    HIPCHK(hipMemcpyAsync(len.data(), g->pathlen.p, npair * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(g->h_poll + 2 * NSEG, g->err.p, 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    if (g->h_poll[2 * NSEG] & ERR_PATH) return PPSP_E_NOPATH;
+    out.path_off.assign(npair + 1, 0);
+    for (uint32_t p = 0; p < npair; p++) out.path_off[p + 1] = out.path_off[p] + len[p];
+    const uint64_t tot = out.path_off[npair];
+    CHK(ensure(g->pathbuf, tot * 4));
+    HIPCHK(hipMemcpyAsync(g->pathoff.p, out.path_off.data(), (npair + 1) * 8, hipMemcpyHostToDevice, st));
+    HIPCHK(launch_path_write(A, pd, g->pathlen.as<uint32_t>(), g->pathoff.as<uint64_t>(), g->pathbuf.as<uint32_t>(), st));
+    out.path.resize(tot);
+    if (tot) HIPCHK(hipMemcpyAsync(out.path.data(), g->pathbuf.p, tot * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    return PPSP_OK;
+}
+
+// Runs one wave of searches to completion in rounds.
+int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
     const uint32_t ns = (uint32_t)P.sd.size(), npair = (uint32_t)P.pairs.size();
     const uint64_t n = g->n;
     const uint64_t ns_words = ((uint64_t)ns + P.G - 1) / P.G * P.G;   // whole groups of G searches
@@ -804,28 +837,199 @@ int run_wave(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
         out.heavy_ms = heavy_ms;
         out.launches = launches;
         out.timed = timed;
-        if (want_path) {
-            CHK(ensure(g->pathlen, npair * 4));
-            CHK(ensure(g->pathoff, (npair + 1) * 8));
-            HIPCHK(launch_path_len(A, g->pairdesc.as<PairDesc>(), g->pathlen.as<uint32_t>(), st));
-            std::vector<uint32_t> len(npair);
-            HIPCHK(hipMemcpyAsync(len.data(), g->pathlen.p, npair * 4, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipMemcpyAsync(g->h_poll + 2 * NSEG, g->err.p, 4, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-            if (g->h_poll[2 * NSEG] & ERR_PATH) return PPSP_E_NOPATH;
-            out.path_off.assign(npair + 1, 0);
-            for (uint32_t p = 0; p < npair; p++) out.path_off[p + 1] = out.path_off[p] + len[p];
-            const uint64_t tot = out.path_off[npair];
-            CHK(ensure(g->pathbuf, tot * 4));
-            HIPCHK(hipMemcpyAsync(g->pathoff.p, out.path_off.data(), (npair + 1) * 8, hipMemcpyHostToDevice, st));
-            HIPCHK(launch_path_write(A, g->pairdesc.as<PairDesc>(), g->pathlen.as<uint32_t>(),
-                                     g->pathoff.as<uint64_t>(), g->pathbuf.as<uint32_t>(), st));
-            out.path.resize(tot);
-            if (tot) HIPCHK(hipMemcpyAsync(out.path.data(), g->pathbuf.p, tot * 4, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-        }
+        if (want_path) CHK(read_paths(g, A, g->pairdesc.as<PairDesc>(), npair, out));
         return PPSP_OK;
     }
+}
+
+// ---- resident searches --------------------------------------------------------
+
+// Whether the wave runs as resident searches, one workgroup per query
+// (resident.hip): independent queries (bidirectional pairs, or searches
+// without partner copies) on a graph of small degrees whose frontiers stay
+// small, with nothing asked for that only the round kernels do (learned,
+// traced and rho schedules, dense frontiers, the heuristic memo, the pull
+// pass, the no-allocation scratch), and no option set that shapes rounds.
+bool resident_ok(ppsp_graph g, const Plan &P) {
+    if (!g->opt_resident || t_arena || g->ml || g->memo_call || g->pull_call || dense_on(g)) return false;
+    if (!g->compact) return false;
+    if (g->opt_profile || g->opt_rounds_per_sync != 16 || g->opt_grid_blocks || g->opt_use_graph || g->opt_queue_cap ||
+        g->opt_local != 16 || g->opt_local_plain || g->opt_local_fill || g->opt_min_chunk != 16 ||
+        g->opt_local_small != 4 || g->opt_local_pct != 90 || g->opt_defer_pct != 105)
+        return false;
+    // A few queries on a large graph leave the chip to the round kernels,
+    // which put every unit on one query and with a heuristic advance several
+    // hops a round. Measured on corner-to-corner pairs, resident / rounds in
+    // ms: BiD-A* on 2048^2 (n = 2^22) x1 42 / 23, x4 42 / 32, x16 45 / 53,
+    // on 1024^2 x1 about 3 / 4; BiDS on 2048^2 x1 37 / 43, x4 38 / 63, on
+    // 4096^2 x1 193 / 104, x8 175 / 199; all distances on 2048^2 48 / 79.
+    const uint64_t nq = P.sd.size() / (P.pair2 ? 2 : 1), n = g->n;
+    const bool heur = is_astar_kind(P.sd[0].kind);
+    if (heur ? n > 3ull << 19 && nq < n >> 18 : n > 1ull << 22 && nq < n >> 21) return false;
+    if (P.pair2) return P.G == 2 && P.pairs.size() * 2 == P.sd.size();
+    if (P.G != 1) return false;
+    for (const SearchDesc &d : P.sd) {
+        if (d.rev || d.pend > d.pbeg + 1) return false;
+        if (d.pend > d.pbeg && !(P.partners[d.pbeg].other & TARGET_BIT)) return false;
+    }
+    return true;
+}
+
+// Runs the wave as resident searches; *redo receives the queries whose
+// frontier outgrew its queue (the round kernels run those).
+int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std::vector<uint32_t> &redo) {
+    const uint32_t ns = (uint32_t)P.sd.size(), npair = (uint32_t)P.pairs.size(), per = P.pair2 ? 2 : 1, nq = ns / per;
+    const uint64_t n = g->n;
+    hipStream_t st = g->st;
+    const bool heur = is_astar_kind(P.sd[0].kind);
+    // distances: the round kernels' state buffer, at half the size
+    CHK(ensure(g->S, (uint64_t)ns * n * 4));
+    // a lattice's frontier grows with the root of n; a queue index has 16 bits
+    const uint32_t spcap = (uint32_t)std::min<uint64_t>(4 * n, std::min<uint64_t>(60000, std::max<uint64_t>(16384, n / 256)));
+    CHK(ensure(g->rspill, (uint64_t)nq * 4 * spcap * 16));
+    // one upload: descriptors, partners, pair roots, steps
+    auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
+    const uint64_t o_part = up(ns * sizeof(SearchDesc)), o_pair = o_part + up(P.partners.size() * sizeof(Partner)),
+                   o_delta = o_pair + up(npair * sizeof(PairDesc)), o_begin = up(o_delta + ns * 8ull), in_bytes = o_begin + 8;
+    std::vector<char> h(in_bytes);
+    memset(h.data() + o_begin, 0xFF, 8);
+    memcpy(h.data(), P.sd.data(), ns * sizeof(SearchDesc));
+    if (!P.partners.empty()) memcpy(h.data() + o_part, P.partners.data(), P.partners.size() * sizeof(Partner));
+    if (npair) memcpy(h.data() + o_pair, P.pairs.data(), npair * sizeof(PairDesc));
+    memcpy(h.data() + o_delta, P.delta.data(), ns * 8ull);
+    CHK(ensure(g->rin, in_bytes));
+    const uint64_t o_stat = up(npair * 8ull), out_bytes = o_stat + (uint64_t)nq * RS_N * 8;
+    CHK(ensure(g->rout, out_bytes));
+    HIPCHK(hipMemsetAsync(g->S.p, 0xFF, (uint64_t)ns * n * 4, st));
+    HIPCHK(hipMemcpyAsync(g->rin.p, h.data(), in_bytes, hipMemcpyHostToDevice, st));
+    ResidentArgs R;
+    memset(&R, 0, sizeof(R));
+    R.row_ptr = g->row_ptr.as<uint32_t>();
+    R.in_row_ptr = g->symmetric ? R.row_ptr : g->in_row_ptr.as<uint32_t>();
+    R.arcs = g->arcs.as<uint2>();
+    R.in_arcs = g->symmetric ? R.arcs : g->in_arcs.as<uint2>();
+    R.xy = g->has_xy ? g->xy.as<int2>() : nullptr;
+    R.ws2 = g->ws2;
+    R.fb = g->fb;
+    R.n = g->n;
+    R.sd = g->rin.as<SearchDesc>();
+    R.partners = (const Partner *)(g->rin.as<char>() + o_part);
+    R.delta = (const uint64_t *)(g->rin.as<char>() + o_delta);
+    R.nquery = nq;
+    R.D = g->S.as<uint32_t>();
+    R.spill = g->rspill.as<uint4>();
+    R.spcap = spcap;
+    R.mu = g->rout.as<uint64_t>();
+    R.qstat = (unsigned long long *)(g->rout.as<char>() + o_stat);
+    R.theta_mode = (uint32_t)g->opt_theta_mode;
+    R.ticks = (unsigned long long)g->opt_timeout_ms * g->clock_khz;
+    R.t_begin = (unsigned long long *)(g->rin.as<char>() + o_begin);
+    // 1,024 threads a query: 256 pairs on the 256^2 grid take 1.36 ms (512 threads: 1.42), 64 BiD-A* pairs on the
+    // 2048^2 lattice 29 ms (41), 1,000 of them 95 (109). Where queries queue for the compute units and are small,
+    // two workgroups a unit do more: 1,000 pairs on the grid 2.9 ms (1,024 threads: 3.8), 4,000 pairs 9.0 (12.9).
+    const int threads = nq > 2 * (uint32_t)g->cu && n <= 1u << 18 ? 512 : 1024;
+    HIPCHK(launch_resident(R, P.pair2, heur, !g->symmetric, threads, st));
+    const PairDesc *pd = (const PairDesc *)(g->rin.as<char>() + o_pair);
+    RoundArgs A;
+    set_args(g, A, ns, npair, P.G, P.pair2);
+    A.sd = R.sd;
+    A.mu = R.mu;
+    A.D32 = R.D;
+    if (P.gather) HIPCHK(launch_gather(A, pd, st));
+    std::vector<char> ho(out_bytes);
+    HIPCHK(hipMemcpyAsync(ho.data(), g->rout.p, out_bytes, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    out.d32 = true;
+    out.mu.assign((uint64_t *)ho.data(), (uint64_t *)ho.data() + npair);
+    const unsigned long long *qs = (const unsigned long long *)(ho.data() + o_stat);
+    for (uint32_t q = 0; q < nq; q++, qs += RS_N) {
+        if (qs[RS_STATUS] & RES_OVERFLOW) return PPSP_E_OVERFLOW;
+        if (qs[RS_STATUS] & RES_TIMEOUT) return PPSP_E_TIMEOUT;
+        if (qs[RS_STATUS] & RES_SPILL) redo.push_back(q);
+        out.stats[ST_ROUNDS] = std::max(out.stats[ST_ROUNDS], qs[RS_ROUNDS]);
+        out.stats[ST_ENTRIES] += qs[RS_ENTRIES];
+        out.stats[ST_SCANV] += qs[RS_SCANV];
+        out.stats[ST_SCANE] += qs[RS_SCANE];
+        out.stats[ST_SUCC] += qs[RS_SUCC];
+        out.stats[ST_CARRY] += qs[RS_CARRY];
+    }
+    out.launches = 1;
+    if (want_path) {
+        // no walk for a query that has to run again: its paths come from that run
+        if (!redo.empty()) {
+            std::vector<uint8_t> again(nq, 0);
+            for (uint32_t q : redo) again[q] = 1;
+            for (uint32_t p = 0; p < npair; p++)
+                if (again[P.pairs[p].a / per]) HIPCHK(hipMemsetAsync(A.mu + p, 0xFF, 8, st));
+        }
+        CHK(ensure(g->err, 16));
+        HIPCHK(hipMemsetAsync(g->err.p, 0, 16, st));
+        A.err = g->err.as<uint32_t>();
+        CHK(read_paths(g, A, pd, npair, out));
+    }
+    return PPSP_OK;
+}
+
+// The queries `redo` (ascending) of plan P as a plan of their own; slot maps its pair slots to P's.
+Plan sub_plan(const Plan &P, const std::vector<uint32_t> &redo, std::vector<uint32_t> &slot) {
+    Plan R;
+    R.G = P.G;
+    R.pair2 = P.pair2;
+    R.gather = P.gather;
+    const uint32_t per = P.pair2 ? 2 : 1;
+    std::vector<uint32_t> to(P.sd.size(), UINT32_MAX);     // new index of each search
+    for (uint32_t q : redo)
+        for (uint32_t i = per * q; i < per * (q + 1); i++) {
+            to[i] = (uint32_t)R.sd.size();
+            R.sd.push_back(P.sd[i]);
+            R.delta.push_back(P.delta[i]);
+        }
+    for (uint32_t p = 0; p < (uint32_t)P.pairs.size(); p++) {
+        const PairDesc &d = P.pairs[p];
+        if (to[d.a] == UINT32_MAX) continue;
+        const uint32_t np = (uint32_t)R.pairs.size();
+        R.pairs.push_back({to[d.a], P.pair2 ? to[d.b] : d.b});
+        slot.push_back(p);
+        if (P.gather) continue;
+        // every search of the query has one partner entry
+        for (uint32_t i = d.a; i < d.a + per; i++) {
+            SearchDesc &x = R.sd[to[i]];
+            x.pbeg = (uint32_t)R.partners.size();
+            x.pend = x.pbeg + 1;
+            R.partners.push_back({P.pair2 ? to[i ^ 1u] : P.partners[P.sd[i].pbeg].other, np});
+        }
+    }
+    return R;
+}
+
+// Runs one wave of searches to completion: resident where that applies, the
+// rest in rounds.
+int run_wave(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
+    if (!resident_ok(g, P)) return run_rounds(g, P, want_path, out);
+    std::vector<uint32_t> redo, slot;
+    CHK(run_resident(g, P, want_path, out, redo));
+    if (redo.empty()) return PPSP_OK;
+    const Plan R = sub_plan(P, redo, slot);
+    WaveOut w;
+    CHK(run_rounds(g, R, want_path, w));
+    out.d32 = false;
+    for (int k = 0; k < ST_N; k++) out.stats[k] += w.stats[k];
+    out.launches += w.launches;
+    for (size_t k = 0; k < slot.size(); k++) out.mu[slot[k]] = w.mu[k];
+    if (want_path) {
+        std::vector<uint32_t> from(out.mu.size(), UINT32_MAX), path;
+        for (size_t k = 0; k < slot.size(); k++) from[slot[k]] = (uint32_t)k;
+        std::vector<uint64_t> off(1, 0);
+        for (size_t p = 0; p < out.mu.size(); p++) {
+            const WaveOut &o = from[p] == UINT32_MAX ? out : w;
+            const size_t k = from[p] == UINT32_MAX ? p : from[p];
+            path.insert(path.end(), o.path.begin() + o.path_off[k], o.path.begin() + o.path_off[k + 1]);
+            off.push_back(path.size());
+        }
+        out.path = std::move(path);
+        out.path_off = std::move(off);
+    }
+    return PPSP_OK;
 }
 
 // ---- planning ---------------------------------------------------------------
@@ -2202,6 +2406,25 @@ uint64_t ppsp_heuristic_fx(int32_t x0, int32_t y0, int32_t x1, int32_t y1, uint3
     return heur(x0, y0, x1, y1, (uint64_t)w_scale * w_scale, frac_bits);
 }
 
+// Whether the balls of a graph grow slowly, as on roads and grids: a search
+// from three vertices reaches 8,192 vertices only after 24 levels or more (or
+// never). There a query's frontier stays within a resident search's queues;
+// on a random graph of degree 8 (6 levels) it outgrows them after a few
+// rounds, which are then lost: 64 pairs took 1.46 ms against 0.85 in rounds.
+static bool ball_is_deep(uint32_t n, const uint64_t *row_ptr, const uint32_t *col) {
+    for (const uint64_t at : {(uint64_t)0, (uint64_t)n / 2, (uint64_t)n - 1}) {
+        uint32_t root = (uint32_t)at;
+        for (uint32_t k = 0; k < 64 && row_ptr[root + 1] == row_ptr[root]; k++) root = root + 1 < n ? root + 1 : 0;
+        std::unordered_map<uint32_t, uint32_t> level{{root, 0}};
+        std::vector<uint32_t> order{root};
+        for (size_t h = 0; h < order.size() && order.size() < 8192; h++)
+            for (uint64_t e = row_ptr[order[h]]; e < row_ptr[order[h] + 1]; e++)
+                if (level.emplace(col[e], level[order[h]] + 1).second) order.push_back(col[e]);
+        if (order.size() >= 8192 && level[order.back()] < 24) return false;
+    }
+    return true;
+}
+
 int ppsp_graph_create(int device, uint32_t n, uint64_t m, const uint64_t *row_ptr, const uint32_t *col,
                       const uint32_t *w, const int32_t *coord_fx, uint32_t coord_frac_bits, uint32_t w_scale,
                       uint32_t flags, void *hip_stream, ppsp_graph *out) {
@@ -2250,6 +2473,11 @@ int ppsp_graph_create(int device, uint32_t n, uint64_t m, const uint64_t *row_pt
         g->fingerprint = h;
     }
     g->maxdeg = maxdeg;
+    // The mean degree: one unit's arcs a microsecond bound a resident query.
+    // Single BiDS queries on 512^2 neighbourhoods, resident / rounds in ms:
+    // degree 8 2.0 / 4.3, 12 2.9 / 4.0, 24 5.1 / 4.4.
+    g->compact = maxdeg <= RES_MAXDEG && m <= 16ull * n && !(n >> RES_ID_BITS) && !(m >> 28) &&
+                 ball_is_deep(n, row_ptr, col);
     g->hchunks = hchunks;
     for (int k = 0; k < 6; k++) g->hchunks_at[k] = hchunks_at[k];
     auto fail = [&](int rc) {
@@ -2426,6 +2654,8 @@ int ppsp_graph_create(int device, uint32_t n, uint64_t m, const uint64_t *row_pt
     if ((he = hipSetDevice(device)) != hipSuccess) return fail(device_error("hipSetDevice", he));
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess) g->cu = prop.multiProcessorCount;
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) g->clock_khz = khz;
     if ((he = hipStreamCreateWithFlags(&g->st, hipStreamNonBlocking)) != hipSuccess) {
         g->st = nullptr;
         return fail(device_error("hipStreamCreateWithFlags", he));
@@ -2480,6 +2710,7 @@ int ppsp_graph_create(int device, uint32_t n, uint64_t m, const uint64_t *row_pt
         // transpose (in-arcs) for the tight-arc path walk
         trp.assign(n + 1, 0);
         for (uint64_t e = 0; e < m; e++) trp[col[e] + 1]++;
+        for (uint32_t v = 1; v <= n; v++) g->compact = g->compact && trp[v] <= RES_MAXDEG;   // in-degrees
         for (uint32_t v = 0; v < n; v++) trp[v + 1] += trp[v];
         std::vector<uint32_t> pos(trp.begin(), trp.end() - 1);
         tarcs.resize(m);
@@ -2715,12 +2946,12 @@ int ppsp_sssp(ppsp_graph g, uint32_t s, const ppsp_opts *opts, void *hip_stream,
     WaveOut w;
     CHK(run_wave(g, P, false, w));
     accumulate(g, w);
-    std::vector<uint64_t> words(g->n);
-    HIPCHK(hipMemcpyAsync(words.data(), g->S.p, (uint64_t)g->n * 8, hipMemcpyDeviceToHost, g->st));
+    std::vector<uint32_t> words((w.d32 ? 1ull : 2ull) * g->n);
+    HIPCHK(hipMemcpyAsync(words.data(), g->S.p, words.size() * 4, hipMemcpyDeviceToHost, g->st));
     HIPCHK(hipStreamSynchronize(g->st));
     const bool re = !g->iperm.empty();
     for (uint32_t v = 0; v < g->n; v++) {
-        const uint32_t d32 = (uint32_t)(words[v] >> 32);
+        const uint32_t d32 = w.d32 ? words[v] : words[2ull * v + 1];   // the high half of the packed word
         dist[re ? g->iperm[v] : v] = d32 == INF32 ? PPSP_INF : d32;
     }
     g->last.wall_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -2909,6 +3140,7 @@ int ppsp_set_option(ppsp_graph g, const char *name, int64_t v) {
     else if (k == "mem_budget_mb") { if (v < 0) return PPSP_E_INVALID; g->opt_mem_budget_mb = v; }
     else if (k == "default_delta") { if (v < 0) return PPSP_E_INVALID; g->opt_default_delta = v; }
     else if (k == "use_graph") g->opt_use_graph = v;
+    else if (k == "resident") { if (v < 0 || v > 1) return PPSP_E_INVALID; g->opt_resident = v; }
     else if (k == "timeout_ms") { if (v < 0) return PPSP_E_INVALID; g->opt_timeout_ms = v; }
     else if (k == "theta_mode") { if (v < 0 || v > 3) return PPSP_E_INVALID; g->opt_theta_mode = v; }
     else if (k == "queue_cap") { if (v < (int64_t)NSEG || v > (1ll << 31)) return PPSP_E_INVALID; g->qcap = (uint64_t)v; g->opt_queue_cap = v; }
@@ -2980,6 +3212,7 @@ int ppsp_get_option(ppsp_graph g, const char *name, int64_t *v) {
     else if (k == "mem_budget_mb") *v = g->opt_mem_budget_mb;
     else if (k == "default_delta") *v = (int64_t)graph_default_delta(g);
     else if (k == "use_graph") *v = g->opt_use_graph;
+    else if (k == "resident") *v = g->opt_resident;
     else if (k == "timeout_ms") *v = g->opt_timeout_ms;
     else if (k == "theta_mode") *v = g->opt_theta_mode;
     else if (k == "queue_cap") *v = (int64_t)g->qcap;

@@ -96,14 +96,6 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
     return x;
 }
 
-__device__ __forceinline__ uint32_t key_scale(uint32_t kind) { return kind >= K_2DIST ? 2u : 1u; }
-
-// key = scale * delta + hk (see ppsp_dev.h); never negative for a consistent heuristic.
-__device__ __forceinline__ uint64_t key_of(uint32_t kind, uint64_t d, int32_t hk) {
-    const int64_t k = (int64_t)((kind >= K_2DIST ? 2 : 1) * d) + hk;
-    return k < 0 ? 0 : (uint64_t)k;
-}
-
 // Heuristic term of vertex v for a search: 0, h_t(v), h_t(v) - h_s(v) or h_s(v) - h_t(v).
 __device__ __forceinline__ int32_t hterm(const RoundArgs &A, const SearchDesc &sd, uint32_t v) {
     if (sd.kind == K_DIST || sd.kind == K_2DIST) return 0;
@@ -1054,32 +1046,6 @@ __device__ __forceinline__ int control_search(const RoundArgs &A, uint32_t i, ui
     return 2;
 }
 
-// The next threshold from the current one, the smallest key of the next
-// frontier and the step Delta d (key units).
-__device__ __forceinline__ uint64_t step_threshold(uint32_t mode, uint64_t th0, uint64_t mk, uint64_t d) {
-    uint64_t th;
-    if (mode == 3) return INF64;     // Bellman-Ford: extract everything every round
-    if (mode == 0 || mk == INF64) {
-        // Delta*-stepping: the i-th threshold is i * Delta; steps that would
-        // extract nothing are skipped by raising it to the smallest key.
-        th = th0 + d;
-        if (th < th0) th = INF64;
-        if (mk != INF64 && mk > th) th = mk;
-    } else if (mode == 1) {
-        // Bucketed variant: extract the Delta-wide bucket that holds the
-        // smallest key; the threshold stays while that bucket refills.
-        const uint64_t b = mk / d;
-        th = (b + 1 > INF64 / d) ? INF64 : (b + 1) * d - 1;
-        if (th < th0) th = th0;
-    } else {
-        // Sliding window: everything within Delta of the smallest key.
-        th = mk + d - 1;
-        if (th < mk) th = INF64;
-        if (th < th0) th = th0;
-    }
-    return th;
-}
-
 // Upper end of the extraction window of heavy vertices (see RoundArgs::hlim).
 __device__ __forceinline__ uint64_t heavy_limit(uint64_t mk, uint64_t d, uint32_t hwin) {
     if (mk == INF64) return INF64;
@@ -1408,7 +1374,8 @@ __global__ __launch_bounds__(BLOCK) void k_idle(RoundArgs A) {
 }
 
 __device__ __forceinline__ uint32_t dist_of(const RoundArgs &A, uint32_t i, uint32_t v) {
-    return (uint32_t)(A.S[state_index(A.G, A.n, i, v)] >> 32);
+    const uint64_t at = state_index(A.G, A.n, i, v);
+    return A.D32 ? A.D32[at] : (uint32_t)(A.S[at] >> 32);
 }
 
 // A predecessor of v on a shortest path from the root of search i: an

@@ -117,13 +117,69 @@ __host__ __device__ inline uint64_t isqrt_floor(uint64_t q) {
     return x;
 }
 
+// The same for q < 2^64 whose root has at most 32 bits. On the device from a
+// single-precision estimate (relative error below 2^-22, so off by up to 2^10)
+// and one Newton step on the exact 64-bit remainder, then off by at most one;
+// a double-precision square root alone takes more instructions.
+__host__ __device__ inline uint32_t isqrt32(uint64_t q) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const float f = __builtin_amdgcn_sqrtf((float)q);
+    uint32_t x = (uint32_t)f;
+    const int64_t rem = (int64_t)(q - (uint64_t)x * x);
+    x += (uint32_t)(int32_t)rintf((float)rem * (0.5f * __builtin_amdgcn_rcpf(fmaxf(f, 1.f))));
+#else
+    uint32_t x = (uint32_t)sqrt((double)q);
+#endif
+    const uint64_t xx = (uint64_t)x * x;
+    if (xx > q) return x - 1;
+    return xx + 2ull * x < q ? x + 1 : x;
+}
+
 // Euclidean heuristic on fixed-point coordinates:
-// floor(w_scale * |p - p'| / 2^fb) = floor(isqrt(w_scale^2 * d2) / 2^fb).
+// floor(w_scale * |p - p'| / 2^fb) = floor(isqrt(w_scale^2 * d2) / 2^fb),
+// which is isqrt(floor(w_scale^2 * d2 / 4^fb)): the shift comes first, so the
+// root has at most 32 bits (w_scale^2 * d2 < 2^63) and its checks need 32 x
+// 32-bit products only.
 __host__ __device__ inline uint64_t heur(int32_t x0, int32_t y0, int32_t x1, int32_t y1,
                                          uint64_t ws2, uint32_t fb) {
-    int64_t dx = (int64_t)x1 - x0, dy = (int64_t)y1 - y0;
-    uint64_t d2 = (uint64_t)(dx * dx) + (uint64_t)(dy * dy);
-    return isqrt_floor(ws2 * d2) >> fb;
+    const uint32_t dx = x0 > x1 ? (uint32_t)x0 - (uint32_t)x1 : (uint32_t)x1 - (uint32_t)x0;
+    const uint32_t dy = y0 > y1 ? (uint32_t)y0 - (uint32_t)y1 : (uint32_t)y1 - (uint32_t)y0;
+    const uint64_t d2 = (uint64_t)dx * dx + (uint64_t)dy * dy;
+    return isqrt32((ws2 * d2) >> (2 * fb));
+}
+
+__device__ __forceinline__ uint32_t key_scale(uint32_t kind) { return kind >= K_2DIST ? 2u : 1u; }
+
+// key = scale * delta + hk; never negative for a consistent heuristic.
+__device__ __forceinline__ uint64_t key_of(uint32_t kind, uint64_t d, int32_t hk) {
+    const int64_t k = (int64_t)((kind >= K_2DIST ? 2 : 1) * d) + hk;
+    return k < 0 ? 0 : (uint64_t)k;
+}
+
+// The next threshold from the current one, the smallest key of the next
+// frontier and the step Delta d (key units).
+__device__ __forceinline__ uint64_t step_threshold(uint32_t mode, uint64_t th0, uint64_t mk, uint64_t d) {
+    uint64_t th;
+    if (mode == 3) return INF64;     // Bellman-Ford: extract everything every round
+    if (mode == 0 || mk == INF64) {
+        // Delta*-stepping: the i-th threshold is i * Delta; steps that would
+        // extract nothing are skipped by raising it to the smallest key.
+        th = th0 + d;
+        if (th < th0) th = INF64;
+        if (mk != INF64 && mk > th) th = mk;
+    } else if (mode == 1) {
+        // Bucketed variant: extract the Delta-wide bucket that holds the
+        // smallest key; the threshold stays while that bucket refills.
+        const uint64_t b = mk / d;
+        th = (b + 1 > INF64 / d) ? INF64 : (b + 1) * d - 1;
+        if (th < th0) th = th0;
+    } else {
+        // Sliding window: everything within Delta of the smallest key.
+        th = mk + d - 1;
+        if (th < mk) th = INF64;
+        if (th < th0) th = th0;
+    }
+    return th;
 }
 
 // Everything a round needs, passed by value to each kernel.
@@ -145,6 +201,8 @@ struct RoundArgs {
     uint32_t G;                // searches per interleaved group (a power of two)
     uint32_t pair2;            // 1: searches 2q and 2q + 1 are one query's forward and backward copies
     uint64_t *S;               // packed (distance, stamp) words, layout above
+    const uint32_t *D32;       // instead, 32-bit distances in the same layout (path walks and gathers after
+                               // the resident kernel; null: S)
     ulonglong2 *ctl;           // [nsearch] (theta, bound) in key units; bound 0 = finished
     const uint64_t *delta;     // [nsearch] threshold increment (key units)
     uint32_t *done;            // [nsearch]
