@@ -54,9 +54,10 @@ hipError_t launch_mlp_reduce(const float *partial, uint32_t nw, float *grad, hip
 hipError_t launch_mlp_adam(float *P, float *m, float *v, const float *partial, uint32_t nw, float lr, uint32_t t,
                            hipStream_t st);
 hipError_t launch_gather(const RoundArgs &A, const PairDesc *pd, hipStream_t st);
-hipError_t launch_path_len(const RoundArgs &A, const PairDesc *pd, uint32_t *len, hipStream_t st);
-hipError_t launch_path_write(const RoundArgs &A, const PairDesc *pd, const uint32_t *len, const uint64_t *off,
-                             uint32_t *out, hipStream_t st);
+hipError_t launch_path_walk(const RoundArgs &A, const PairDesc *pd, uint32_t *len, uint32_t *vtx, uint32_t cap,
+                            hipStream_t st);
+hipError_t launch_path_write(const RoundArgs &A, const PairDesc *pd, const uint32_t *len, const uint32_t *vtx,
+                             uint32_t cap, const uint64_t *off, uint32_t *out, hipStream_t st);
 }  // namespace ppsp
 
 using namespace ppsp;
@@ -226,7 +227,7 @@ struct ppsp_graph_s {
     // workspace (grow only)
     DevBuf tsum;                    // local-chunk time limit: 4 sums, then 2 limits
     DevBuf S, q0, q1, sd, partners, pairdesc, ctl, delta, done, exh, alive, minkey, mu, qcount, cpre, round, err,
-        stats, wstats, pathlen, pathoff, pathbuf, heavy, hcount, hlim, memo;
+        stats, wstats, pathlen, pathoff, pathbuf, pathvtx, heavy, hcount, hlim, memo;
     uint32_t maxdeg = 0;
     uint64_t hchunks = 0;           // heavy-list chunks of all vertices of degree > HEAVY_DEG
     uint64_t hchunks_at[6] = {};    // the same for degree > 16 << k (k = 0..5), for the "list_deg" option
@@ -469,20 +470,25 @@ struct WaveOut {
 // Path lengths, then the paths of every pair slot of the wave's searches.
 int read_paths(ppsp_graph g, const RoundArgs &A, const PairDesc *pd, uint32_t npair, WaveOut &out) {
     hipStream_t st = g->st;
-    CHK(ensure(g->pathlen, npair * 4));
+    // room for the walks as they are found: 32 MB in all, at least 64 vertices each (longer ones are walked twice)
+    const uint32_t cap = (uint32_t)std::min<uint64_t>(g->n, std::max<uint64_t>(64, (4u << 20) / std::max(1u, npair)));
+    CHK(ensure(g->pathlen, npair * 8ull));
+    CHK(ensure(g->pathvtx, npair * 8ull * cap));
     CHK(ensure(g->pathoff, (npair + 1) * 8));
-    HIPCHK(launch_path_len(A, pd, g->pathlen.as<uint32_t>(), st));
-    std::vector<uint32_t> len(npair);
-    HIPCHK(hipMemcpyAsync(len.data(), g->pathlen.p, npair * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(launch_path_walk(A, pd, g->pathlen.as<uint32_t>(), g->pathvtx.as<uint32_t>(), cap, st));
+    std::vector<uint32_t> len(2 * (size_t)npair);
+    HIPCHK(hipMemcpyAsync(len.data(), g->pathlen.p, npair * 8ull, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(g->h_poll + 2 * NSEG, g->err.p, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (g->h_poll[2 * NSEG] & ERR_PATH) return PPSP_E_NOPATH;
     out.path_off.assign(npair + 1, 0);
-    for (uint32_t p = 0; p < npair; p++) out.path_off[p + 1] = out.path_off[p] + len[p];
+    for (uint32_t p = 0; p < npair; p++)
+        out.path_off[p + 1] = out.path_off[p] + (len[2 * p] ? len[2 * p] + len[2 * p + 1] - 1 : 0);
     const uint64_t tot = out.path_off[npair];
     CHK(ensure(g->pathbuf, tot * 4));
     HIPCHK(hipMemcpyAsync(g->pathoff.p, out.path_off.data(), (npair + 1) * 8, hipMemcpyHostToDevice, st));
-    HIPCHK(launch_path_write(A, pd, g->pathlen.as<uint32_t>(), g->pathoff.as<uint64_t>(), g->pathbuf.as<uint32_t>(), st));
+    HIPCHK(launch_path_write(A, pd, g->pathlen.as<uint32_t>(), g->pathvtx.as<uint32_t>(), cap, g->pathoff.as<uint64_t>(),
+                             g->pathbuf.as<uint32_t>(), st));
     out.path.resize(tot);
     if (tot) HIPCHK(hipMemcpyAsync(out.path.data(), g->pathbuf.p, tot * 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -2741,7 +2747,7 @@ int ppsp_graph_destroy(ppsp_graph g) {
     DevBuf *bufs[] = {&g->row_ptr, &g->arcs, &g->xy, &g->in_row_ptr, &g->in_arcs, &g->S, &g->q0, &g->q1,
                       &g->sd, &g->partners, &g->pairdesc, &g->ctl, &g->delta, &g->done, &g->exh, &g->alive,
                       &g->minkey, &g->mu, &g->qcount, &g->cpre, &g->round, &g->err, &g->stats, &g->wstats, &g->heavy, &g->hcount, &g->pathlen, &g->pathoff,
-                      &g->pathbuf};
+                      &g->pathbuf, &g->pathvtx};
     for (DevBuf *b : bufs) release(*b);
     for (hipEvent_t e : g->ev) (void)hipEventDestroy(e);
     if (g->h_poll) (void)hipHostFree(g->h_poll);
