@@ -283,7 +283,9 @@ def batch_query(h, pairs, opts: Opts, stream=None, want_path=False, path_cap=Non
     dist = np.empty(k, np.uint64)
     off = np.empty(k + 1, np.uint64) if want_path else None
     if want_path and path_cap is None:
-        path_cap = max(1, 64 * k)
+        # 16 MB at least, of which only what is filled is touched: a buffer too small runs the batch again
+        # (16 routes of about 1,000 vertices ran three times from 64 vertices a query: 8.6 ms, 2.5 from this size)
+        path_cap = max(1 << 22, 64 * k)
     vtx = np.empty(path_cap, np.uint32) if want_path else None
     st = stream if stream is not None else current_stream()
     for _ in range(8):
