@@ -125,7 +125,8 @@ typedef struct {
     uint64_t scanned_vertices; /* extracted, unpruned search-vertices whose arcs were relaxed */
     uint64_t scanned_arcs;     /* arcs relaxed */
     uint64_t relax_success;    /* successful write_min operations */
-    uint64_t searches;         /* searches (frontier copies) in the batch */
+    uint64_t searches;         /* searches (frontier copies) in the batch; Multi-BiDS: one per query-graph
+                                  vertex, also where its queries run on searches of their own */
     uint64_t waves;            /* memory waves the batch was split into */
     double wall_ms;            /* host wall time of the call */
     double relax_kernel_ms;    /* summed duration of the timed round-kernel launches ("profile"), else 0 */

@@ -850,6 +850,15 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
 
 // ---- resident searches --------------------------------------------------------
 
+// Entries of each of a resident query's four spill areas (16 bytes an entry). A
+// lattice's frontier grows with the root of n; a queue index has 16 bits. From
+// n = 32,768 (of pairs) the areas and the distances (4n a search) take no more
+// than the query's state in rounds (8n a search).
+uint32_t resident_spill(uint64_t n, uint64_t per) {
+    const uint64_t small = std::min<uint64_t>(4 * n, 4096), share = std::min<uint64_t>(16384, per * n / 16);
+    return (uint32_t)std::min<uint64_t>(60000, std::max({small, share, n / 256}));
+}
+
 // Whether the wave runs as resident searches, one workgroup per query
 // (resident.hip): independent queries (bidirectional pairs, or searches
 // without partner copies) on a graph of small degrees whose frontiers stay
@@ -870,6 +879,9 @@ bool resident_ok(ppsp_graph g, const Plan &P) {
     // on 1024^2 x1 about 3 / 4; BiDS on 2048^2 x1 37 / 43, x4 38 / 63, on
     // 4096^2 x1 193 / 104, x8 175 / 199; all distances on 2048^2 48 / 79.
     const uint64_t nq = P.sd.size() / (P.pair2 ? 2 : 1), n = g->n;
+    const uint64_t per = P.pair2 ? 2 : 1;
+    const uint64_t areas = 64ull * resident_spill(n, per);
+    if (areas > per * n * 4 && nq * (per * n * 4 + areas) > std::max<uint64_t>(state_budget(g), 16 * n)) return false;
     const bool heur = is_astar_kind(P.sd[0].kind);
     if (heur ? n > 3ull << 19 && nq < n >> 18 : n > 1ull << 22 && nq < n >> 21) return false;
     if (P.pair2) return P.G == 2 && P.pairs.size() * 2 == P.sd.size();
@@ -890,8 +902,7 @@ int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std:
     const bool heur = is_astar_kind(P.sd[0].kind);
     // distances: the round kernels' state buffer, at half the size
     CHK(ensure(g->S, (uint64_t)ns * n * 4));
-    // a lattice's frontier grows with the root of n; a queue index has 16 bits
-    const uint32_t spcap = (uint32_t)std::min<uint64_t>(4 * n, std::min<uint64_t>(60000, std::max<uint64_t>(16384, n / 256)));
+    const uint32_t spcap = resident_spill(n, per);
     CHK(ensure(g->rspill, (uint64_t)nq * 4 * spcap * 16));
     // one upload: descriptors, partners, pair roots, steps
     auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
@@ -1006,6 +1017,26 @@ Plan sub_plan(const Plan &P, const std::vector<uint32_t> &redo, std::vector<uint
         }
     }
     return R;
+}
+
+// A shared plan (Multi-BiDS) with every query on its own two searches.
+Plan pairs_apart(const Plan &P) {
+    Plan Q;
+    Q.G = 2;
+    Q.pair2 = true;
+    for (const PairDesc &d : P.pairs) {
+        const uint32_t a = (uint32_t)Q.sd.size(), p = a / 2;
+        for (uint32_t side = 0; side < 2; side++) {
+            const uint32_t i = side ? d.b : d.a;
+            Q.sd.push_back(P.sd[i]);
+            Q.delta.push_back(P.delta[i]);
+            Q.sd.back().pbeg = a + side;
+            Q.sd.back().pend = a + side + 1;
+            Q.partners.push_back({a + (1u - side), p});
+        }
+        Q.pairs.push_back({a, a + 1});
+    }
+    return Q;
 }
 
 // Runs one wave of searches to completion: resident where that applies, the
@@ -1296,8 +1327,18 @@ int run_multi(ppsp_graph g, const std::vector<Query> &qs, const ppsp_opts *o, ui
             P.sd[i].pend = (uint32_t)P.partners.size();
         }
         g->last.searches += P.sd.size();
+        // Resident searches do not share; a query on its own two is faster
+        // all the same. BiDS pairs over query-graph vertices on the 1024^2
+        // lattice, shared in rounds / resident, ms: 250 over 251 (a star) 195
+        // / 10, 192 over 200 73 / 11, 250 over 40 60 / 11, 600 over 378 85 /
+        // 22, 500 over 40 66 / 19, 1,500 over 100 122 / 47 (2.6 times as fast
+        // at 15 pairs a vertex: beyond, shared).
+        Plan Q;
+        const size_t np = P.pairs.size();
+        if (g->opt_multi_group == 32 && 2 * np <= search_limit(g) && np <= 16 * P.sd.size())
+            Q = pairs_apart(P);
         WaveOut w;
-        CHK(run_wave(g, P, want_path, w));
+        CHK(run_wave(g, !Q.sd.empty() && resident_ok(g, Q) ? Q : P, want_path, w));
         accumulate(g, w);
         collect(w, ans_of_pair, ans, want_path);
         wave_comps.clear();

@@ -138,6 +138,30 @@ def test_frontier_beyond_the_queue_runs_in_rounds(P):
     assert np.array_equal(G.batch_query(pairs, algo="sssp", batch="vc", delta=1 << 30), exp)
 
 
+@pytest.mark.parametrize("symmetric", [True, False])
+@pytest.mark.parametrize("verts,k,resident", [(2, 1, True), (9, 36, True), (33, 528, True), (36, 630, False), (300, 200, True)])
+def test_shared_batches(P, symmetric, verts, k, resident):
+    """Multi-BiDS: every query on its own searches up to 16 pairs a query-graph vertex, shared beyond; with paths."""
+    g = gen.lattice(60, 0.1, seed=30)
+    rng = np.random.default_rng(31)
+    if not symmetric:
+        g.w = (g.w + rng.integers(0, 800, g.w.size)).astype(np.uint32)
+        g.symmetric = False
+    v = rng.choice(g.n, verts, replace=False)
+    pairs = np.array([(v[i], v[j]) for i in range(verts) for j in range(i)])
+    pairs = pairs[rng.choice(len(pairs), k, replace=False)].astype(np.uint32)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = _open(P, g)
+    dist, (off, vtx) = G.batch_query(pairs, algo="bids", batch="multi", want_path=True)
+    assert np.array_equal(dist, exp)
+    if symmetric:      # on a directed graph a vertex is two of the query graph: a source and a target
+        assert (G.stats()["relax_launches"] == 1) == resident
+        assert G.stats()["searches"] == len(np.unique(pairs))
+    for q in range(k):
+        assert oracle.check_path(g.n, g.row_ptr, g.col, g.w, vtx[off[q]:off[q + 1]], int(pairs[q, 0]),
+                                 int(pairs[q, 1]), int(exp[q])) == (0, 0), q
+
+
 def test_directed_paths_and_all_distances(P):
     g = gen.lattice(90, 0.1, seed=18)
     rng = np.random.default_rng(19)
