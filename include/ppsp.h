@@ -573,7 +573,8 @@ int ppsp_last_stats(ppsp_graph g, ppsp_stats *stats);
  *                     step window, "heavy_window"); graphs without a vertex above 512 have no
  *                     hub list
  *   "heavy_claim"     hub-list records (chunks of at most 2,048 arcs) a wave of the hub-list
- *                     kernel claims at a time from a shared counter (1 to 64; default 4)
+ *                     kernel claims at a time from a shared counter (1 to 64; default 4); a list that
+ *                     is short for the grid is dealt out in pieces of records instead
  *   "heavy_waves"     single-wave workgroups per CU of the hub-list kernel (1 to 32; default
  *                     24; 0: the round kernel's grid)
  *   "heavy_grouped"   1 (default): on a symmetric graph with vertices of degree > 512 and a

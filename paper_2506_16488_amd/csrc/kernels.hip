@@ -253,17 +253,6 @@ __device__ __forceinline__ bool relax_to(const RoundArgs &A, const SearchDesc &s
     return relax_commit<MEMO>(A, sd, i, v, cand, other, old, bnd, stamp, out, lmin, succ, kout, dense);
 }
 
-// The same for arc e of the search's CSR (the transpose for a backward
-// search on a directed graph).
-template <bool MEMO, bool REV>
-__device__ __forceinline__ bool relax_arc(const RoundArgs &A, const SearchDesc &sd, uint32_t i, uint32_t u,
-                                          uint32_t du, uint64_t bnd, uint32_t e, uint32_t stamp, uint4 *out,
-                                          uint64_t *lmin, unsigned long long *succ, uint64_t *kout, bool dense) {
-    (void)u;
-    const uint2 a = ((REV && sd.rev) ? A.in_arcs : A.arcs)[e];
-    return relax_to<MEMO>(A, sd, i, a, du, bnd, stamp, out, lmin, succ, kout, dense);
-}
-
 // Dense frontiers (RoundArgs::dbits): sets v^(i)'s bit in the bitmap of the
 // step bucket of key k. Returns false when that bucket lies beyond the ring;
 // the caller then queues the entry.
@@ -838,10 +827,86 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
 }
 
 
-// The heavy list, relaxed by every wave of the grid: each wave takes whole
-// chunks (at most HEAVY_CHUNK arcs of one vertex), 64 arcs per step. Runs
-// after k_round in the same round, on the same grid, so it too must keep 5
-// waves per SIMD resident.
+#ifndef HEAVY_WAYS
+#define HEAVY_WAYS 2   // arcs per lane in flight in the hub-list kernel
+#endif
+
+// Arcs b .. e - 1 of u^(ai), at distance du, HEAVY_WAYS a lane and step: their
+// loads, then their state loads, then their WriteMins are in flight together.
+// The search's statistics are merged once, at the end.
+template <bool MEMO, bool REV>
+__device__ __forceinline__ void relax_piece(const RoundArgs &A, WaveStage &st, uint32_t &scnt, uint32_t ai, uint32_t du,
+                                            uint32_t b, uint32_t e, uint32_t np, uint32_t stamp, uint4 *qout,
+                                            uint32_t *qcout, bool count, unsigned long long *c_succ) {
+    const SearchDesc sd = A.sd[ai];
+    const uint64_t bnd = A.ctl[ai].y;
+    const bool dm = A.dbits && A.dmode[ai];
+    const uint2 *arcs = (REV && sd.rev) ? A.in_arcs : A.arcs;
+    uint64_t lmin = INF64;
+    uint32_t added = 0;
+    for (uint32_t e0 = b; e0 < e; e0 += HEAVY_WAYS * WAVE) {
+        uint2 arc[HEAVY_WAYS];
+        uint64_t cand[HEAVY_WAYS], other[HEAVY_WAYS], old[HEAVY_WAYS];
+        unsigned long long *wp[HEAVY_WAYS];
+        bool want[HEAVY_WAYS];
+#pragma unroll
+        for (int h = 0; h < HEAVY_WAYS; h++) {
+            const uint32_t x = e0 + h * WAVE + lane_id();
+            want[h] = x < e;
+            arc[h] = want[h] ? arcs[x] : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int h = 0; h < HEAVY_WAYS; h++) {
+            cand[h] = (uint64_t)du + arc[h].y;
+            other[h] = INF64;
+            wp[h] = nullptr;
+            old[h] = 0;
+            if (want[h]) {                              // possibly stale: never below the truth
+                if (A.pair2) {
+                    const uint64_t base = state_index(A.G, A.n, ai & ~1u, arc[h].x);
+                    const ulonglong2 w = *(const ulonglong2 *)(A.S + base);
+                    old[h] = (ai & 1) ? w.y : w.x;
+                    other[h] = (ai & 1) ? w.x : w.y;
+                    wp[h] = (unsigned long long *)(A.S + base + (ai & 1));
+                } else {
+                    wp[h] = (unsigned long long *)(A.S + state_index(A.G, A.n, ai, arc[h].x));
+                    old[h] = *wp[h];
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < HEAVY_WAYS; h++) {
+            if (want[h] && cand[h] >= INF32) { atomicOr(A.err, ERR_OVERFLOW); want[h] = false; }
+            want[h] = want[h] && cand[h] < (old[h] >> 32);
+            old[h] = want[h] ? atomicMin(wp[h], (cand[h] << 32) | stamp) : 0ull;
+        }
+#pragma unroll
+        for (int h = 0; h < HEAVY_WAYS; h++) {
+            if (__ballot(want[h]) == 0) continue;
+            bool app = false;
+            uint4 ne = make_uint4(0, 0, 0, 0);
+            uint64_t kv = INF64;
+            if (want[h])
+                app = relax_commit<MEMO>(A, sd, ai, arc[h].x, cand[h], other[h], old[h], bnd, stamp, &ne, &lmin, c_succ, &kv, dm);
+            if (app && dm && dense_add(A, ai, ne.y, kv)) app = false;
+            added += app;
+            wstage_push(st, scnt, app, ne, qout, qcout, A.qseg, A.err);
+        }
+    }
+    search_stats(A, np, ai, added, lmin, count);
+}
+
+// The heavy list, relaxed by every wave of the grid. Runs after k_round in
+// the same round.
+//
+// A step of a wave (64 arcs a way) is a chain of dependent accesses of 2 to 3
+// us, so a list that is short for the grid is cut up, into as many parts a
+// record (2, 4, 8 or 16) as leave a wave at most 32 pieces. Four BiDS queries
+// on R-MAT 20 (about 4,000 records a round): whole records 22.0 ms, at most 2
+// pieces a wave 12.1, 4 10.2, 8 9.2, 16 8.2, 32 8.1, 64 8.4. On R-MAT 22 with
+// 128 queries (141,000 records) whole records are as fast as parts (456 ms;
+// 458 in 8, 463 in 16). One or four arcs a lane in flight instead of two: 1 %
+// slower, the same.
 template <bool MEMO, bool REV>
 __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
     __shared__ WaveStage st;
@@ -855,34 +920,37 @@ __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
     uint4 *qout = ((r & 1) ? A.q0 : A.q1) + (uint64_t)sego * A.qseg;
     uint32_t *qcout = &A.qcount[np * NSEG + sego];
     unsigned long long c_succ = 0;
-    // Records are claimed hclaim at a time from a counter (hcount[1], cleared
-    // with the list by the control step), so a wave that drew short records
-    // takes more; every wave leaves once the counter has passed the list.
+    uint32_t parts = 1;
+    while (parts < 16 && nh * parts * 2 <= 32ull * gridDim.x) parts <<= 1;
+    const uint32_t len = HEAVY_CHUNK / parts;
+    // Cut up, piece k is part k / nh of record k % nh (the parts that a short
+    // record lacks come last). Whole records are claimed hclaim at a time from
+    // a counter (hcount[1], cleared with the list by the control step), so a
+    // wave that drew short ones takes more. Every wave leaves once it has
+    // passed the last piece.
+    uint32_t k = parts > 1 ? blockIdx.x : 0, end = parts > 1 ? (uint32_t)nh * parts : 0;
     for (;;) {
-        unsigned long long got = 0;
-        if (lane_id() == 0) got = atomicAdd(A.hcount + 1, (unsigned long long)A.hclaim);
-        // wave-uniform in a scalar register, so the records load through the scalar cache
-        const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)nh));
-        if (base >= nh) break;
-        const uint32_t end = (uint32_t)min((uint64_t)base + A.hclaim, nh);
-        for (uint32_t slot = base; slot < end; slot++) {
-            const uint4 h1 = A.heavy[2 * slot];
-            const uint32_t ee = A.heavy[2 * slot + 1].x;
-            const uint32_t ai = h1.x;
-            const SearchDesc sd = A.sd[ai];
-            const uint64_t bnd = A.ctl[ai].y;
-            const bool dm = A.dbits && A.dmode[ai];
-            for (uint32_t e0 = h1.w; e0 < ee; e0 += WAVE) {
-                const uint32_t e = e0 + lane_id();
-                bool app = false;
-                uint4 ne = make_uint4(0, 0, 0, 0);
-                uint64_t lmin = INF64, kv = INF64;
-                if (e < ee) app = relax_arc<MEMO, REV>(A, sd, ai, h1.y, h1.z, bnd, e, stamp, &ne, &lmin, &c_succ, &kv, dm);
-                if (app && dm && dense_add(A, ai, ne.y, kv)) app = false;
-                wstage_push(st, scnt, app, ne, qout, qcout, A.qseg, A.err);
-                search_stats(A, np, ai, app ? 1u : 0u, lmin, count);
+        uint32_t slot = k, part = 0;
+        if (parts > 1) {
+            if (k >= end) break;
+            part = k / (uint32_t)nh;
+            slot = k % (uint32_t)nh;
+            k += gridDim.x;
+        } else {
+            if (k == end) {
+                unsigned long long got = 0;
+                if (lane_id() == 0) got = atomicAdd(A.hcount + 1, (unsigned long long)A.hclaim);
+                // wave-uniform in a scalar register, so the records load through the scalar cache
+                k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)nh));
+                if (k >= nh) break;
+                end = (uint32_t)min((uint64_t)k + A.hclaim, nh);
             }
+            slot = k++;
         }
+        const uint4 h1 = A.heavy[2 * (uint64_t)slot];
+        const uint32_t ee = A.heavy[2 * (uint64_t)slot + 1].x, b = h1.w + part * len;
+        if (b < ee)
+            relax_piece<MEMO, REV>(A, st, scnt, h1.x, h1.z, b, min(ee, b + len), np, stamp, qout, qcout, count, &c_succ);
     }
     wstage_flush(st, scnt, qout, qcout, A.qseg, A.err);
     c_succ = wave_sum_u64(c_succ);

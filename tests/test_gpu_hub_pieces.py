@@ -1,0 +1,57 @@
+"""The hub-list kernel's pieces of records: lists from one record to more than
+the grid takes in parts, hubs of every length around a part, a chunk and their
+multiples, directed graphs and dense frontiers, against the oracle."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2506_16488_amd as P
+    P.lib()
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    return P
+
+
+def _hubs(seed):
+    """Hubs of 513 to 8,193 leaves (parts are 128 to 2,048 arcs) in a chain, the leaves shared between neighbours."""
+    rng = np.random.default_rng(seed)
+    degs = [513, 514, 639, 640, 641, 767, 768, 769, 1023, 1024, 1025, 2047, 2048, 2049, 2175, 2176, 2177, 4095, 4096,
+            4097, 6143, 6145, 8191, 8192, 8193]
+    leaves, k = 20000, len(degs)
+    src = [np.arange(k - 1)]
+    dst = [np.arange(1, k)]
+    for h, d in enumerate(degs):
+        src.append(np.full(d, h))
+        dst.append(k + rng.choice(leaves, d, replace=False))
+    src, dst = np.concatenate(src), np.concatenate(dst)
+    return gen.csr_from_edges(k + leaves, src, dst, rng.integers(1, 1000, src.size))
+
+
+@pytest.mark.parametrize("waves", [1, 24, 32])
+@pytest.mark.parametrize("symmetric", [True, False])
+def test_hub_pieces(P, symmetric, waves):
+    g = _hubs(1)
+    if not symmetric:
+        g.w = (g.w + np.random.default_rng(2).integers(0, 50, g.w.size)).astype(np.uint32)
+        g.symmetric = False
+    pairs = gen.pairs_uniform(g.n, 600, seed=3)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = P.Graph.from_host(g)
+    G.set_option("timeout_ms", 60000)
+    G.set_option("heavy_waves", waves)
+    G.set_option("heavy_window", 1)
+    for k in (1, 40, 600):          # few records (16 parts each) to several thousand a round
+        for algo in ("bids", "et", "sssp"):
+            print("hub pieces", symmetric, waves, k, algo, flush=True)
+            assert np.array_equal(G.batch_query(pairs[:k], algo=algo), exp[:k]), (k, algo)
+    assert G.stats()["heavy_arcs"] > 0
+    if symmetric:
+        G.set_option("dense_min", 64)
+        assert np.array_equal(G.batch_query(pairs, algo="bids", delta=3000), exp)
