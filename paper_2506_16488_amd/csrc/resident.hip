@@ -338,8 +338,14 @@ __global__ __launch_bounds__(B) void k_resident(ResidentArgs A) {
         for (uint32_t c0 = 0;; c0 += B) {
             // 2. Check and prune the candidates, and bid for the heads of their arcs.
             const unsigned long long tag = (unsigned long long)(15u - (gen & 15u)) << 60;
-            // (an even share for each wave: the shortest chain of each)
-            const uint32_t batch = min(cand - c0, (uint32_t)B), share = (batch + NW - 1) / NW;
+            // An even share for each wave, but 32 candidates (two steps of
+            // arcs) before more than the four waves of the four SIMDs take
+            // part: a wave costs its instructions however few its lanes. (An
+            // even share alone, and of the bids below: 8 BiD-A* queries on
+            // 1024^2 15.9 ms instead of 15.0, one query on a 256^2 grid 0.32
+            // instead of 0.305.)
+            const uint32_t batch = min(cand - c0, (uint32_t)B);
+            const uint32_t share = max((batch + NW - 1) / NW, min(32u, (batch + 3) / 4));
             const uint32_t first = min(wave * share, batch), mine = min(share, batch - first), base = c0 + first;
             if (mine) {
                 Entry e = {0, 0, 0};
@@ -449,11 +455,10 @@ __global__ __launch_bounds__(B) void k_resident(ResidentArgs A) {
             __syncthreads();
             const uint32_t nbid = min(uniform(s_nbid), BIDS);
             // 3. The smallest bid of a vertex is its new distance.
-            const uint32_t bshare = min((nbid + NW - 1) / NW, 64u);
-            for (uint32_t b0 = wave * bshare; b0 < nbid; b0 += NW * bshare) {
+            for (uint32_t b0 = wave * 64; b0 < nbid; b0 += B) {
                 Entry e = {0, 0, 0};
                 bool app = false, again = false;
-                if (lane < bshare && b0 + lane < nbid) {
+                if (b0 + lane < nbid) {
                     const uint4 x = s_bid[b0 + lane];
                     const uint32_t v = x.x & ~SIDE_BIT;
                     const unsigned long long b = tag | (unsigned long long)x.y << 28 | (x.x >> 4 & 0x8000000u) | v;
