@@ -354,6 +354,7 @@ constexpr uint32_t RECHECK_Z = 0xFFFFFFFEu;
 // SIMD a fifth of the workgroups would start only when others finish, and
 // the static chunk stride would leave them a tail: 1.5x the launch time on
 // the 2048^2 lattice).
+constexpr uint32_t DTILE_RUN = 32;   // words of a run
 template <bool PULL, bool MEMO, bool REV, bool DENSE>
 __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
     __shared__ WaveStage st;
@@ -364,6 +365,12 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
     // Dense frontiers: after its queue chunks a wave takes tiles of 64 words
     // (2,048 vertices) of the read bitmaps of the searches in this round's
     // dense list, one word per lane, and extracts their set bits 64 at a time.
+    // A tile is WAVE / DTILE_RUN runs of DTILE_RUN words from all over the
+    // bitmap, and the tiles of the searches alternate: the vertices of large
+    // degree lie together (numbered first), and in tiles of 64 words on end,
+    // search after search, a few waves took most of the arcs. 128 queries on
+    // R-MAT 22: so 456 ms; alternating searches 422, with runs of 32 words 408,
+    // 16 413, 8 433, 4 456 (shorter runs fetch lines for a part of them).
     const uint32_t ndense = DENSE ? A.dcount[par] : 0u;
     const uint64_t tiles_per = DENSE ? (A.dwords + WAVE - 1) / WAVE : 1ull;
     const uint64_t dtiles = (uint64_t)ndense * tiles_per;
@@ -462,8 +469,8 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
             if (!__any(dword != 0)) {
                 // the next tile; its words are cleared as they are read (no adds
                 // go to a read bitmap: refills of the current bucket use the other one)
-                dsi = A.dlist[(uint64_t)par * A.nsearch + dt / tiles_per];
-                dwidx = (dt % tiles_per) * WAVE + lane_id();
+                dsi = A.dlist[(uint64_t)par * A.nsearch + dt % ndense];
+                dwidx = (dt / ndense + lane_id() / DTILE_RUN * tiles_per) * DTILE_RUN + lane_id() % DTILE_RUN;
                 dt += gridDim.x;
                 dword = 0;
                 if (dwidx < A.dwords) {
