@@ -396,6 +396,7 @@ void set_args(ppsp_graph g, RoundArgs &A, uint32_t nsearch, uint32_t npair, uint
     A.hcount = g->hcount.as<unsigned long long>();
     A.hcap = g->maxdeg > HEAVY_DEG ? g->hcap : 0;
     A.hclaim = (uint32_t)g->opt_heavy_claim;
+    A.hbins = 1;
     A.list_deg = t_arena ? HEAVY_DEG : (uint32_t)g->opt_list_deg;
     A.hlim = g->hlim.as<uint64_t>();
     A.hwin = (uint32_t)g->opt_heavy_window;
@@ -504,7 +505,7 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
     const uint64_t sbytes = ns_words * n * 8;
     CHK(ensure(g->S, sbytes));
     CHK(ensure(g->round, 16));
-    CHK(ensure(g->hcount, 16));
+    CHK(ensure(g->hcount, HCOUNT_WORDS * 8));
     if (g->maxdeg > HEAVY_DEG) {
         // a round can extract each hub once per search; a quarter of that at once is ample
         // (inside the no-allocation scratch: a quarter of the hub chunks, at least 4,096)
@@ -516,6 +517,14 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
     }
     // the hub list grouped by vertex: symmetric graphs with hubs, state groups of 4 or more searches
     const bool hgrouped = g->nhub && g->opt_heavy_grouped && P.G >= 4 && !t_arena;
+    // The hub list in bins by pair of searches, of room for every hub of both:
+    // from 16 pairs, two a die (the kernel's comment has the figures), where
+    // that room is at most 2 GB.
+    bool hbinned = !hgrouped && !t_arena && ns >= 32 && (uint64_t)ns * list_chunks(g) <= 1u << 26;
+    if (hbinned && g->maxdeg > HEAVY_DEG && g->hcap < ns * list_chunks(g)) {
+        g->hcap = (uint32_t)(ns * list_chunks(g));
+        CHK(ensure(g->heavy, (uint64_t)g->hcap * 32));
+    }
     const uint64_t ngroups = ns_words / P.G;
     if (hgrouped) {
         CHK(ensure(g->hmask, 2ull * g->nhub * ngroups * 8));
@@ -578,7 +587,7 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
         HIPCHK(hipMemsetAsync(g->tsum.p, 0, 48, st));
         HIPCHK(hipMemsetAsync(g->wstats.p, 0, (uint64_t)wgrid * ST_N * 8, st));
         HIPCHK(hipMemsetAsync(g->round.p, 0, 16, st));
-        HIPCHK(hipMemsetAsync(g->hcount.p, 0, 16, st));
+        HIPCHK(hipMemsetAsync(g->hcount.p, 0, HCOUNT_WORDS * 8, st));
         HIPCHK(hipMemsetAsync(g->err.p, 0, 16, st));
         HIPCHK(hipMemsetAsync(g->stats.p, 0, ST_N * 8, st));
         // dense frontiers: by size (options), or by the learned schedule's mode
@@ -642,6 +651,11 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
         }
         RoundArgs A;
         set_args(g, A, ns, npair, P.G, P.pair2);
+        if (A.hcap && hbinned) {
+            while (A.hbins < HBINS && A.hbins * 4 <= ns) A.hbins *= 2;
+            if (A.hbins < 16 || A.hcap / A.hbins < 4096) A.hbins = 1;
+            A.hbcap = A.hcap / A.hbins;
+        }
         if (hgrouped) {
             A.hgrouped = 1;
             A.list_deg = HEAVY_DEG;              // grouped records index the hubs
@@ -796,7 +810,9 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
                 if (want > (1ull << 31)) return PPSP_E_OOM;
                 g->qcap = want;
             }
-            if (errbits & ERR_HEAVY) {
+            if (A.hbins > 1 && (errbits & ERR_HEAVY)) {
+                hbinned = false;                           // one bin was full: the list as a whole
+            } else if (errbits & ERR_HEAVY) {
                 if (g->hcap >= (1u << 28)) return PPSP_E_OOM;
                 g->hcap *= 4;
                 CHK(ensure(g->heavy, (uint64_t)g->hcap * 32));

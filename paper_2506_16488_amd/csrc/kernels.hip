@@ -639,16 +639,23 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
                     atomicOr(A.hmask + ((uint64_t)par * A.nhub + hid) * A.ngroups + grp, 1ull << (si & (A.G - 1)));
                 if (old != 0) nck = 0;
             }
-            uint32_t tot;
-            const uint32_t pre = wave_exscan(nck, &tot);
-            unsigned long long b0 = 0;
-            if (lane_id() == 0 && tot) b0 = atomicAdd(A.hgrouped ? A.hgcount + par : A.hcount, (unsigned long long)tot);
-            b0 = __shfl(b0, 0);
+            unsigned long long b0 = 0, lim = A.hcap;
+            if (A.hbins > 1) {
+                const uint32_t bin = (si >> 1) & (A.hbins - 1);
+                const uint64_t first = (uint64_t)bin * A.hbcap;
+                lim = first + A.hbcap;
+                if (heavy) b0 = first + atomicAdd(A.hcount + hbin_count(bin), (unsigned long long)nck);
+            } else {
+                uint32_t tot;
+                const uint32_t pre = wave_exscan(nck, &tot);
+                if (lane_id() == 0 && tot) b0 = atomicAdd(A.hgrouped ? A.hgcount + par : A.hcount, (unsigned long long)tot);
+                b0 = __shfl(b0, 0) + pre;
+            }
             for (uint32_t k = 0; k < nck; k++) {
-                const uint64_t slot = b0 + pre + k;
+                const uint64_t slot = b0 + k;
                 const uint32_t eb = rb + k * HEAVY_CHUNK;
                 const uint32_t ee = min(re, eb + HEAVY_CHUNK);
-                if (slot >= A.hcap) {
+                if (slot >= lim) {
                     atomicOr(A.err, ERR_HEAVY);
                 } else if (A.hgrouped) {
                     A.hrec[(uint64_t)par * A.hcap + slot] = make_uint4(hid, grp, eb, ee);
@@ -834,6 +841,18 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
 }
 
 
+// Records in bin b of the hub list.
+__device__ __forceinline__ uint32_t hbin_size(const RoundArgs &A, uint32_t b) {
+    return (uint32_t)min(A.hcount[hbin_count(b)], (unsigned long long)A.hbcap);
+}
+
+// Empties the bins and their claims, by `many` lanes of one workgroup.
+__device__ __forceinline__ void hbins_reset(const RoundArgs &A, bool here, uint32_t lane, uint32_t many) {
+    if (!here || A.hbins == 1) return;
+    for (uint32_t b = lane; b < A.hbins; b += many) A.hcount[hbin_count(b)] = 0;
+    if (lane < XCDS) A.hcount[hbin_claim(lane)] = 0;
+}
+
 #ifndef HEAVY_WAYS
 #define HEAVY_WAYS 2   // arcs per lane in flight in the hub-list kernel
 #endif
@@ -914,50 +933,101 @@ __device__ __forceinline__ void relax_piece(const RoundArgs &A, WaveStage &st, u
 // 128 queries (141,000 records) whole records are as fast as parts (456 ms;
 // 458 in 8, 463 in 16). One or four arcs a lane in flight instead of two: 1 %
 // slower, the same.
-template <bool MEMO, bool REV>
+//
+// In bins (BINS) workgroup b, which runs on die b % 8, takes the pairs of
+// searches p with p % 8 = b % 8, one after the other. A long list is bound by
+// scattered lines from beyond the L2 (10.5 G in 200 ms: 52 G/s, the card's rate
+// for them), 78 % of its accesses where every die works on all pairs at once;
+// the words of the hubs of one pair stay in a die's L2 while it works on that
+// pair alone. 128 queries on R-MAT 22: rounds of the longest lists 7.7 ms
+// before, 5.0 in bins, the batch 408 / 342. A short list (in parts) is dealt
+// out within each die: with claims a round of 0.18 ms took 0.34.
+template <bool MEMO, bool REV, bool BINS>
 __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
     __shared__ WaveStage st;
     uint32_t scnt = 0;
     const uint32_t r = A.round[1];                          // set by this round's k_round
     const uint32_t np = (r & 1) ^ 1, stamp = r + 1;
-    const uint64_t nh = min((uint64_t)*A.hcount, (uint64_t)A.hcap);
-    if (nh == 0) return;
     const bool count = A.sc && blockIdx.x < ML_SAMPLE;   // scaled like the round kernel's counts
     const uint32_t sego = blockIdx.x % NSEG;
     uint4 *qout = ((r & 1) ? A.q0 : A.q1) + (uint64_t)sego * A.qseg;
     uint32_t *qcout = &A.qcount[np * NSEG + sego];
     unsigned long long c_succ = 0;
+    uint64_t nh = 0;
+    if (BINS) {
+        uint32_t mine = 0;
+        for (uint32_t b = lane_id(); b < A.hbins; b += WAVE) mine += hbin_size(A, b);
+        nh = wave_sum_u64(mine);
+    } else {
+        nh = min((uint64_t)*A.hcount, (uint64_t)A.hcap);
+    }
+    if (nh == 0) return;
     uint32_t parts = 1;
     while (parts < 16 && nh * parts * 2 <= 32ull * gridDim.x) parts <<= 1;
     const uint32_t len = HEAVY_CHUNK / parts;
-    // Cut up, piece k is part k / nh of record k % nh (the parts that a short
-    // record lacks come last). Whole records are claimed hclaim at a time from
-    // a counter (hcount[1], cleared with the list by the control step), so a
-    // wave that drew short ones takes more. Every wave leaves once it has
-    // passed the last piece.
-    uint32_t k = parts > 1 ? blockIdx.x : 0, end = parts > 1 ? (uint32_t)nh * parts : 0;
-    for (;;) {
-        uint32_t slot = k, part = 0;
-        if (parts > 1) {
-            if (k >= end) break;
-            part = k / (uint32_t)nh;
-            slot = k % (uint32_t)nh;
-            k += gridDim.x;
-        } else {
-            if (k == end) {
-                unsigned long long got = 0;
-                if (lane_id() == 0) got = atomicAdd(A.hcount + 1, (unsigned long long)A.hclaim);
-                // wave-uniform in a scalar register, so the records load through the scalar cache
-                k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)nh));
-                if (k >= nh) break;
-                end = (uint32_t)min((uint64_t)k + A.hclaim, nh);
-            }
-            slot = k++;
-        }
-        const uint4 h1 = A.heavy[2 * (uint64_t)slot];
-        const uint32_t ee = A.heavy[2 * (uint64_t)slot + 1].x, b = h1.w + part * len;
+    const auto piece = [&](uint64_t slot, uint32_t part) {
+        const uint4 h1 = A.heavy[2 * slot];
+        const uint32_t ee = A.heavy[2 * slot + 1].x, b = h1.w + part * len;
         if (b < ee)
             relax_piece<MEMO, REV>(A, st, scnt, h1.x, h1.z, b, min(ee, b + len), np, stamp, qout, qcout, count, &c_succ);
+    };
+    if (BINS) {
+        // this die's bins, then (of a long list) those of the next
+        for (uint32_t v = 0; v < XCDS; v++) {
+            const uint32_t x = (blockIdx.x + v) % XCDS, own = x + XCDS * lane_id();
+            // lane l: the records of the die's bins up to its l-th (HBINS / XCDS of them at most)
+            uint32_t upto = own < A.hbins ? hbin_size(A, own) : 0;
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const uint32_t y = __shfl_up(upto, o);
+                if (lane_id() >= (uint32_t)o) upto += y;
+            }
+            const uint32_t recs = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1), pieces = recs * parts;
+            // pieces k, k + step .. below end: dealt out (a short list), or
+            // hclaim records claimed from the die's counter
+            uint32_t k = blockIdx.x / XCDS, end = pieces, step = (gridDim.x + XCDS - 1) / XCDS;
+            do {
+                if (parts == 1) {
+                    unsigned long long got = 0;
+                    if (lane_id() == 0 && recs) got = atomicAdd(A.hcount + hbin_claim(x), (unsigned long long)A.hclaim);
+                    k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)recs));
+                    end = min(k + A.hclaim, recs);
+                    step = 1;
+                }
+                for (; k < end; k += step) {
+                    const uint32_t rec = k % recs, l = (uint32_t)__popcll(__ballot(upto <= rec));
+                    const uint32_t before = l ? (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)l - 1) : 0u;
+                    piece((uint64_t)(x + XCDS * l) * A.hbcap + (rec - before), k / recs);
+                }
+            } while (parts == 1 && end < recs);
+            if (parts > 1) break;
+        }
+    } else {
+        // Cut up, piece k is part k / nh of record k % nh (the parts that a short
+        // record lacks come last). Whole records are claimed hclaim at a time from
+        // a counter (hcount[1], cleared with the list by the control step), so a
+        // wave that drew short ones takes more. Every wave leaves once it has
+        // passed the last piece.
+        uint32_t k = parts > 1 ? blockIdx.x : 0, end = parts > 1 ? (uint32_t)nh * parts : 0;
+        for (;;) {
+            uint32_t slot = k, part = 0;
+            if (parts > 1) {
+                if (k >= end) break;
+                part = k / (uint32_t)nh;
+                slot = k % (uint32_t)nh;
+                k += gridDim.x;
+            } else {
+                if (k == end) {
+                    unsigned long long got = 0;
+                    if (lane_id() == 0) got = atomicAdd(A.hcount + 1, (unsigned long long)A.hclaim);
+                    // wave-uniform in a scalar register, so the records load through the scalar cache
+                    k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)nh));
+                    if (k >= nh) break;
+                    end = (uint32_t)min((uint64_t)k + A.hclaim, nh);
+                }
+                slot = k++;
+            }
+            piece(slot, part);
+        }
     }
     wstage_flush(st, scnt, qout, qcout, A.qseg, A.err);
     c_succ = wave_sum_u64(c_succ);
@@ -1145,6 +1215,7 @@ __global__ __launch_bounds__(BLOCK) void k_control(RoundArgs A) {
         A.hcount[1] = 0;
         if (A.hgrouped) A.hgcount[np] = 0;       // the list whose bits the hub-list kernel just cleared
     }
+    hbins_reset(A, blockIdx.x == 0, threadIdx.x, BLOCK);
     if (i >= A.nsearch) return;
     uint64_t mk = 0, nb = 0;
     if (control_search(A, i, par, np, true, &mk, &nb) != 2) return;
@@ -1230,6 +1301,7 @@ __global__ __launch_bounds__(WAVE) void k_control_ml(RoundArgs A) {
             if (A.hgrouped) A.hgcount[np] = 0;   // the list whose bits the hub-list kernel just cleared
         }
     }
+    hbins_reset(A, blockIdx.x == 0, lane, WAVE);
     // share of this round's chunks that the counting workgroups processed
     const uint32_t nch = A.cpre[par * (NSEG + 1) + NSEG];
     const uint32_t q = nch / A.grid, rem = nch % A.grid;
@@ -1591,13 +1663,19 @@ hipError_t launch_round(const RoundArgs &A, uint32_t grid, hipStream_t st, hipEv
                   : launch_round_t<false, false, false>(A, grid, st, e0, e1);
 }
 
-template <bool MEMO, bool REV>
+template <bool MEMO, bool REV, bool BINS>
 static hipError_t launch_heavy_t(const RoundArgs &A, uint32_t grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     if (e0)
-        hipExtLaunchKernelGGL(k_heavy<MEMO, REV>, dim3(grid), dim3(WAVE), 0, st, e0, e1, 0, A);
+        hipExtLaunchKernelGGL(k_heavy<MEMO, REV, BINS>, dim3(grid), dim3(WAVE), 0, st, e0, e1, 0, A);
     else
-        k_heavy<MEMO, REV><<<grid, WAVE, 0, st>>>(A);
+        k_heavy<MEMO, REV, BINS><<<grid, WAVE, 0, st>>>(A);
     return hipGetLastError();
+}
+
+template <bool MEMO, bool REV>
+static hipError_t launch_heavy_t(const RoundArgs &A, uint32_t grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+    return A.hbins > 1 ? launch_heavy_t<MEMO, REV, true>(A, grid, st, e0, e1)
+                       : launch_heavy_t<MEMO, REV, false>(A, grid, st, e0, e1);
 }
 
 template <bool MEMO>

@@ -72,6 +72,12 @@ constexpr int BLOCK = 256;                     // threads per block (four wave64
 constexpr int WAVE = 64;
 constexpr int WSTAGE = 256;                    // LDS staging slots per wave (round kernel)
 constexpr uint32_t HEAVY_DEG = 512;            // extracted vertices above this go to the heavy list
+constexpr uint32_t XCDS = 8;                   // dies of the chip, each with an L2; workgroups go to them in turn
+constexpr uint32_t HBINS = 256;                // most bins of the hub list (RoundArgs::hbins)
+// words of RoundArgs::hcount: a bin's chunks, a die's claims; a line each
+__host__ __device__ constexpr uint32_t hbin_count(uint32_t b) { return 8 * (1 + b); }
+__host__ __device__ constexpr uint32_t hbin_claim(uint32_t x) { return 8 * (1 + HBINS + x); }
+constexpr uint32_t HCOUNT_WORDS = 8 * (1 + HBINS + XCDS);
 constexpr uint32_t HEAVY_CHUNK = 2048;         // arcs per heavy-list chunk
 constexpr int NSEG = 64;                       // append segments of a frontier queue
 
@@ -218,7 +224,9 @@ struct RoundArgs {
     uint32_t *round;           // [0] round to run next (read by k_round), [1] round just run (k_control)
     uint4 *heavy;              // [hcap][2] arc chunks of this round's extracted high-degree vertices:
                                //   (search, vertex, distance, first arc), (end arc, 0, 0, 0)
-    unsigned long long *hcount;  // [0] chunks written this round, [1] claim counter of the hub-list kernel
+    unsigned long long *hcount;  // [0] chunks written this round, [1] claim counter of the hub-list kernel;
+                                 // in bins: [hbin_count(b)], [hbin_claim(x)]
+    uint32_t hbins, hbcap;     // bins of the list by pair of searches (a power of two, 16 to HBINS, or 1); room of one
     uint32_t hclaim;           // hub-list records a wave claims at a time
     uint32_t list_deg;         // extracted vertices of higher degree go to the hub list (at most HEAVY_DEG)
     uint32_t hcap;             // heavy list capacity (chunks); 0 = no heavy path

@@ -55,3 +55,22 @@ def test_hub_pieces(P, symmetric, waves):
     if symmetric:
         G.set_option("dense_min", 64)
         assert np.array_equal(G.batch_query(pairs, algo="bids", delta=3000), exp)
+
+
+@pytest.mark.parametrize("k", [15, 16, 17, 100, 300])
+def test_hub_bins(P, k):
+    """The hub list in bins by pair: below and above 16 pairs, more pairs than bins, with few and
+    with many waves, whole records claimed and pieces dealt out."""
+    g = _hubs(5)
+    pairs = gen.pairs_uniform(g.n, k, seed=k)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = P.Graph.from_host(g)
+    G.set_option("timeout_ms", 60000)
+    for window in (1, 64):
+        G.set_option("heavy_window", window)
+        for waves, claim in ((24, 4), (1, 1), (0, 64)):
+            G.set_option("heavy_waves", waves)
+            G.set_option("heavy_claim", claim)
+            for algo in ("bids", "et"):
+                print("hub bins", k, window, waves, algo, flush=True)
+                assert np.array_equal(G.batch_query(pairs, algo=algo), exp), (window, waves, algo)
