@@ -354,7 +354,6 @@ constexpr uint32_t RECHECK_Z = 0xFFFFFFFEu;
 // SIMD a fifth of the workgroups would start only when others finish, and
 // the static chunk stride would leave them a tail: 1.5x the launch time on
 // the 2048^2 lattice).
-constexpr uint32_t DTILE_RUN = 32;   // words of a run
 template <bool PULL, bool MEMO, bool REV, bool DENSE>
 __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
     __shared__ WaveStage st;
@@ -365,16 +364,20 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
     // Dense frontiers: after its queue chunks a wave takes tiles of 64 words
     // (2,048 vertices) of the read bitmaps of the searches in this round's
     // dense list, one word per lane, and extracts their set bits 64 at a time.
-    // A tile is WAVE / DTILE_RUN runs of DTILE_RUN words from all over the
-    // bitmap, and the tiles of the searches alternate: the vertices of large
-    // degree lie together (numbered first), and in tiles of 64 words on end,
-    // search after search, a few waves took most of the arcs. 128 queries on
-    // R-MAT 22: so 456 ms; alternating searches 422, with runs of 32 words 408,
-    // 16 413, 8 433, 4 456 (shorter runs fetch lines for a part of them).
+    // The vertices of large degree lie together (numbered first). So a sweep of
+    // the grid over the tiles, search after search (the chip works on few
+    // searches at a time, whose lines stay near), deals them to other waves
+    // each time: without, a few waves took most of the arcs. And where a sweep
+    // spans more than one bitmap, a tile is four runs of 16 words from its four
+    // quarters. R-MAT 22 x 128 queries / R-MAT 24 x 256, ms: tiles on end, dealt
+    // alike in each sweep 445 / 2,360; in turn 378 / 2,285; in turn and in runs
+    // of 32 336 / 2,446, 16 319 / 2,686. (Searches alternating, as tiles of two
+    // runs, 342 / 3,124.)
     const uint32_t ndense = DENSE ? A.dcount[par] : 0u;
-    const uint64_t tiles_per = DENSE ? (A.dwords + WAVE - 1) / WAVE : 1ull;
-    const uint64_t dtiles = (uint64_t)ndense * tiles_per;
-    uint64_t dt = blockIdx.x, dwidx = 0;
+    const uint32_t tiles_per = DENSE ? (uint32_t)((A.dwords + WAVE - 1) / WAVE) : 1u;
+    const uint32_t dtiles = ndense * tiles_per;            // state of 16 KB each: far below 2^32
+    const uint32_t run = tiles_per < gridDim.x ? 4 : 6;       // log2 of the words of a run
+    uint32_t dsweep = 0, dturn = blockIdx.x, dwidx = 0;    // first tile of the sweep, this wave's place in it
     uint32_t dword = 0, dsi = 0;
     if (DENSE && blockIdx.x == 0 && lane_id() == 0) {
         A.dcount[np] = 0;                                  // the list the control step builds next
@@ -465,13 +468,16 @@ __global__ __launch_bounds__(WAVE, 5) void k_round(RoundArgs A) {
                 search_stats(A, np, ent.x & ~CARRY_BIT, valid ? 1u : 0u, k, false);
                 continue;
             }
-        } else if (DENSE && (__any(dword != 0) || dt < dtiles)) {
+        } else if (DENSE && (__any(dword != 0) || dsweep + dturn < dtiles)) {
             if (!__any(dword != 0)) {
                 // the next tile; its words are cleared as they are read (no adds
                 // go to a read bitmap: refills of the current bucket use the other one)
-                dsi = A.dlist[(uint64_t)par * A.nsearch + dt % ndense];
-                dwidx = (dt / ndense + lane_id() / DTILE_RUN * tiles_per) * DTILE_RUN + lane_id() % DTILE_RUN;
-                dt += gridDim.x;
+                const uint32_t dt = dsweep + dturn;
+                dsi = A.dlist[(uint64_t)par * A.nsearch + dt / tiles_per];
+                dwidx = ((dt % tiles_per + (lane_id() >> run) * tiles_per) << run) + (lane_id() & ((1u << run) - 1u));
+                dsweep += gridDim.x;
+                dturn += (uint32_t)(gridDim.x * 0.618f) | 1u;    // the golden ratio: no short cycle (at 5 / 8: 2,453 ms on R-MAT 24)
+                if (dturn >= gridDim.x) dturn -= gridDim.x;
                 dword = 0;
                 if (dwidx < A.dwords) {
                     uint32_t *wp = A.dbits + ((uint64_t)dsi * (A.dring + 1) + A.dread[dsi]) * A.dwords + dwidx;
