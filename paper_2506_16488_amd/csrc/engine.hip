@@ -300,8 +300,10 @@ uint32_t round_grid(ppsp_graph g) {
     return g->opt_grid_blocks > 0 ? (uint32_t)g->opt_grid_blocks : (uint32_t)(20 * g->cu);
 }
 
-// The hub-list kernel takes its records from a counter, so its grid is free
-// of the round kernel's (option "heavy_waves": single-wave workgroups per CU).
+// The hub-list kernel deals out its list (pieces of records among its
+// workgroups, by die where the list is in bins, or records from a counter)
+// over whatever grid it has, so its grid is free of the round kernel's (option
+// "heavy_waves": single-wave workgroups per CU).
 uint32_t heavy_grid(ppsp_graph g) {
     return g->opt_heavy_waves > 0 ? (uint32_t)(g->opt_heavy_waves * g->cu) : round_grid(g);
 }
@@ -653,7 +655,8 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
         set_args(g, A, ns, npair, P.G, P.pair2);
         if (A.hcap && hbinned) {
             while (A.hbins < HBINS && A.hbins * 4 <= ns) A.hbins *= 2;
-            if (A.hbins < 16 || A.hcap / A.hbins < 4096) A.hbins = 1;
+            // a die without a workgroup has nobody to take its bins
+            if (A.hbins < 16 || A.hcap / A.hbins < 4096 || heavy_grid(g) < XCDS) A.hbins = 1;
             A.hbcap = A.hcap / A.hbins;
         }
         if (hgrouped) {

@@ -988,9 +988,11 @@ __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
                 if (lane_id() >= (uint32_t)o) upto += y;
             }
             const uint32_t recs = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1), pieces = recs * parts;
-            // pieces k, k + step .. below end: dealt out (a short list), or
-            // hclaim records claimed from the die's counter
-            uint32_t k = blockIdx.x / XCDS, end = pieces, step = (gridDim.x + XCDS - 1) / XCDS;
+            // pieces k, k + step .. below end: dealt out (a short list) among the
+            // workgroups that the die has, at least one (the host keeps one list
+            // for a grid below XCDS), or hclaim records claimed from the die's
+            // counter
+            uint32_t k = blockIdx.x / XCDS, end = pieces, step = die_blocks(gridDim.x, x);
             do {
                 if (parts == 1) {
                     unsigned long long got = 0;

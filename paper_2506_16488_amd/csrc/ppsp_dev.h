@@ -78,6 +78,10 @@ constexpr uint32_t HBINS = 256;                // most bins of the hub list (Rou
 __host__ __device__ constexpr uint32_t hbin_count(uint32_t b) { return 8 * (1 + b); }
 __host__ __device__ constexpr uint32_t hbin_claim(uint32_t x) { return 8 * (1 + HBINS + x); }
 constexpr uint32_t HCOUNT_WORDS = 8 * (1 + HBINS + XCDS);
+// Workgroups of die x in a grid of `grid` (workgroup b is on die b % XCDS): not
+// the same for every die unless the grid is a multiple of XCDS. Workgroup b is
+// number b / XCDS of its die, and takes every die_blocks-th piece from there.
+__host__ __device__ constexpr uint32_t die_blocks(uint32_t grid, uint32_t x) { return (grid + XCDS - 1 - x) / XCDS; }
 constexpr uint32_t HEAVY_CHUNK = 2048;         // arcs per heavy-list chunk
 constexpr int NSEG = 64;                       // append segments of a frontier queue
 

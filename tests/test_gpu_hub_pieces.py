@@ -74,3 +74,21 @@ def test_hub_bins(P, k):
             for algo in ("bids", "et"):
                 print("hub bins", k, window, waves, algo, flush=True)
                 assert np.array_equal(G.batch_query(pairs, algo=algo), exp), (window, waves, algo)
+
+
+@pytest.mark.parametrize("grid", [4, 8, 20, 100, 301])
+def test_hub_bins_any_grid(P, grid):
+    """Grids of the hub-list kernel that the chip's 8 dies do not share evenly, and one that leaves dies empty."""
+    g = _hubs(6)
+    pairs = gen.pairs_uniform(g.n, 40, seed=60)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = P.Graph.from_host(g)
+    G.set_option("timeout_ms", 60000)
+    G.set_option("heavy_waves", 0)
+    G.set_option("grid_blocks", grid)
+    for window in (1, 64):
+        G.set_option("heavy_window", window)
+        for algo in ("bids", "et", "sssp"):
+            print("hub bins, grid", grid, window, algo, flush=True)
+            assert np.array_equal(G.batch_query(pairs, algo=algo), exp), (window, algo)
+    assert G.stats()["heavy_arcs"] > 0
