@@ -519,12 +519,15 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
     }
     // the hub list grouped by vertex: symmetric graphs with hubs, state groups of 4 or more searches
     const bool hgrouped = g->nhub && g->opt_heavy_grouped && P.G >= 4 && !t_arena;
-    // The hub list in bins by pair of searches, of room for every hub of both:
-    // from 16 pairs, two a die (the kernel's comment has the figures), where
-    // that room is at most 2 GB.
-    bool hbinned = !hgrouped && !t_arena && ns >= 32 && (uint64_t)ns * list_chunks(g) <= 1u << 26;
-    if (hbinned && g->maxdeg > HEAVY_DEG && g->hcap < ns * list_chunks(g)) {
-        g->hcap = (uint32_t)(ns * list_chunks(g));
+    // The hub list in bins by pair of searches: from 16 pairs, two a die (the
+    // kernel's comment has the figures), where room for every hub of all the
+    // pairs of a bin, as many for each as for the fullest, is at most 2 GB.
+    uint32_t hbins = 1;
+    while (hbins < HBINS && hbins * 4 <= ns) hbins *= 2;
+    const uint64_t hroom = (uint64_t)hbins * ((ns + 2 * hbins - 1) / (2 * hbins)) * 2 * list_chunks(g);
+    bool hbinned = !hgrouped && !t_arena && ns >= 32 && hroom <= 1u << 26;
+    if (hbinned && g->maxdeg > HEAVY_DEG && g->hcap < hroom) {
+        g->hcap = (uint32_t)hroom;
         CHK(ensure(g->heavy, (uint64_t)g->hcap * 32));
     }
     const uint64_t ngroups = ns_words / P.G;
@@ -654,7 +657,7 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
         RoundArgs A;
         set_args(g, A, ns, npair, P.G, P.pair2);
         if (A.hcap && hbinned) {
-            while (A.hbins < HBINS && A.hbins * 4 <= ns) A.hbins *= 2;
+            A.hbins = hbins;
             // a die without a workgroup has nobody to take its bins
             if (A.hbins < 16 || A.hcap / A.hbins < 4096 || heavy_grid(g) < XCDS) A.hbins = 1;
             A.hbcap = A.hcap / A.hbins;

@@ -92,3 +92,22 @@ def test_hub_bins_any_grid(P, grid):
             print("hub bins, grid", grid, window, algo, flush=True)
             assert np.array_equal(G.batch_query(pairs, algo=algo), exp), (window, algo)
     assert G.stats()["heavy_arcs"] > 0
+
+
+def test_hub_bins_of_uneven_pairs(P):
+    """24 pairs of searches in 16 bins: a bin of two pairs has room for all the hubs of both, so the wave runs once."""
+    rng = np.random.default_rng(7)
+    n, d = 40000, 30
+    src = np.concatenate([np.repeat(np.arange(n), d), np.zeros(600, np.int64)])
+    dst = np.concatenate([rng.integers(0, n, n * d), 1 + np.arange(600)])
+    g = gen.csr_from_edges(n, src, dst, np.ones(src.size, np.uint32))
+    pairs = rng.permutation(n)[:96].reshape(-1, 2).astype(np.uint32)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = P.Graph.from_host(g)
+    G.set_option("timeout_ms", 60000)
+    G.set_option("list_deg", 16)
+    G.set_option("queue_cap", 1 << 23)
+    G.set_option("heavy_window", 1)
+    for _ in range(2):
+        assert np.array_equal(G.batch_query(pairs, algo="sssp", delta=1 << 20), exp)
+        assert G.stats()["retries"] == 0 and G.stats()["heavy_chunks"] > 0
