@@ -521,14 +521,23 @@ int run_rounds(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
     const bool hgrouped = g->nhub && g->opt_heavy_grouped && P.G >= 4 && !t_arena;
     // The hub list in bins by pair of searches: from 16 pairs, two a die (the
     // kernel's comment has the figures), where room for every hub of all the
-    // pairs of a bin, as many for each as for the fullest, is at most 2 GB.
+    // pairs of a bin, as many for each as for the fullest, is at most 2 GB (and,
+    // beside the search state, within an explicit "mem_budget_mb"). Where the
+    // device has no such room the list stays one, of a quarter of it.
     uint32_t hbins = 1;
     while (hbins < HBINS && hbins * 4 <= ns) hbins *= 2;
     const uint64_t hroom = (uint64_t)hbins * ((ns + 2 * hbins - 1) / (2 * hbins)) * 2 * list_chunks(g);
     bool hbinned = !hgrouped && !t_arena && ns >= 32 && hroom <= 1u << 26;
     if (hbinned && g->maxdeg > HEAVY_DEG && g->hcap < hroom) {
+        const uint32_t one = g->hcap;
         g->hcap = (uint32_t)hroom;
-        CHK(ensure(g->heavy, (uint64_t)g->hcap * 32));
+        if ((g->opt_mem_budget_mb > 0 && sbytes + (hroom - one) * 32 > state_budget(g)) ||
+            ensure(g->heavy, hroom * 32) != PPSP_OK) {
+            hbinned = false;
+            g->hcap = one;
+            CHK(ensure(g->heavy, (uint64_t)one * 32));
+            g_last_error.clear();
+        }
     }
     const uint64_t ngroups = ns_words / P.G;
     if (hgrouped) {
