@@ -346,7 +346,7 @@ uint64_t state_budget(ppsp_graph g) {
     if (g->opt_mem_budget_mb > 0) return (uint64_t)g->opt_mem_budget_mb << 20;
     size_t fr = 0, tot = 0;
     if (hipMemGetInfo(&fr, &tot) != hipSuccess) { (void)hipGetLastError(); return 1ull << 30; }
-    uint64_t have = fr + g->S.bytes + g->dbits.bytes;   // reusable
+    uint64_t have = fr + g->S.bytes + g->dbits.bytes + g->rspill.bytes;   // reusable
     // queues (at their largest default size), the hub list, trace buffers and small buffers
     uint64_t reserve = (2ull << 30) + 2 * std::max<uint64_t>(g->qcap, 1ull << 28) * 16 +
                        (g->maxdeg > HEAVY_DEG ? (1ull << 26) * 32 : 0) + (1ull << 30);
@@ -924,17 +924,23 @@ bool resident_ok(ppsp_graph g, const Plan &P) {
     return true;
 }
 
-// Runs the wave as resident searches; *redo receives the queries whose
-// frontier outgrew its queue (the round kernels run those).
+// The buffers of a wave of resident searches that grow with it: distances (the
+// round kernels' state buffer, at half the size) and spill areas.
+int resident_room(ppsp_graph g, const Plan &P) {
+    const uint64_t ns = P.sd.size(), per = P.pair2 ? 2 : 1;
+    CHK(ensure(g->S, ns * g->n * 4));
+    return ensure(g->rspill, ns / per * 4 * resident_spill(g->n, per) * 16);
+}
+
+// Runs the wave as resident searches, in the buffers of resident_room; *redo
+// receives the queries whose frontier outgrew its queue (the round kernels run
+// those).
 int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std::vector<uint32_t> &redo) {
     const uint32_t ns = (uint32_t)P.sd.size(), npair = (uint32_t)P.pairs.size(), per = P.pair2 ? 2 : 1, nq = ns / per;
     const uint64_t n = g->n;
     hipStream_t st = g->st;
     const bool heur = is_astar_kind(P.sd[0].kind);
-    // distances: the round kernels' state buffer, at half the size
-    CHK(ensure(g->S, (uint64_t)ns * n * 4));
     const uint32_t spcap = resident_spill(n, per);
-    CHK(ensure(g->rspill, (uint64_t)nq * 4 * spcap * 16));
     // one upload: descriptors, partners, pair roots, steps
     auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
     const uint64_t o_part = up(ns * sizeof(SearchDesc)), o_pair = o_part + up(P.partners.size() * sizeof(Partner)),
@@ -1070,16 +1076,30 @@ Plan pairs_apart(const Plan &P) {
     return Q;
 }
 
-// Runs one wave of searches to completion: resident where that applies, the
-// rest in rounds.
+// run_rounds, which may take the memory of the resident searches' spill areas.
+int run_rounds_alone(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
+    const int rc = run_rounds(g, P, want_path, out);
+    if (rc != PPSP_E_OOM || !g->rspill.p) return rc;
+    release(g->rspill);
+    g_last_error.clear();
+    out = WaveOut{};
+    return run_rounds(g, P, want_path, out);
+}
+
+// Runs one wave of searches to completion: resident where that applies (and
+// its buffers fit the device), the rest in rounds.
 int run_wave(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out) {
-    if (!resident_ok(g, P)) return run_rounds(g, P, want_path, out);
+    if (!resident_ok(g, P)) return run_rounds_alone(g, P, want_path, out);
+    if (resident_room(g, P) != PPSP_OK) {
+        g_last_error.clear();
+        return run_rounds_alone(g, P, want_path, out);
+    }
     std::vector<uint32_t> redo, slot;
     CHK(run_resident(g, P, want_path, out, redo));
     if (redo.empty()) return PPSP_OK;
     const Plan R = sub_plan(P, redo, slot);
     WaveOut w;
-    CHK(run_rounds(g, R, want_path, w));
+    CHK(run_rounds_alone(g, R, want_path, w));
     out.d32 = false;
     for (int k = 0; k < ST_N; k++) out.stats[k] += w.stats[k];
     out.launches += w.launches;
@@ -2148,6 +2168,7 @@ int srv_setup_graph(ppsp_server srv, SrvGraph &G, const ppsp_opts &o, uint64_t b
     G.slot_q.assign(G.C, 0);
     hipStream_t st = g->st;
     CHK(set_device(g));
+    release(g->rspill);      // a server's queries run in rounds
     CHK(ensure(g->S, (uint64_t)ns * n * 8));
     CHK(ensure(g->round, 16));
     CHK(ensure(g->hcount, 16));

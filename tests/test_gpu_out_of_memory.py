@@ -98,3 +98,34 @@ G.set_option("mem_budget_mb", (state >> 20) + 8)
 assert np.array_equal(G.batch_query(pairs, algo="bids"), exp)
 assert G.get_option("heavy_cap") < room and G.stats()["waves"] == 1
 """)
+
+
+ROADS = r"""
+g = gen.grid(64, 64, 1, 1000, seed=7)
+pairs = np.random.default_rng(8).permutation(g.n)[:128].reshape(-1, 2).astype(np.uint32)
+exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+G = P.Graph.from_host(g)
+G.set_option("timeout_ms", 60000)
+spill = 64 * 4 * 4096 * 16                                    # four areas of 4,096 entries a query
+"""
+
+
+def test_resident_falls_back_to_rounds(tmp_path):
+    _run(tmp_path, ROADS + r"""
+refuse(spill)
+for algo in ("bids", "et"):
+    assert np.array_equal(G.batch_query(pairs, algo=algo), exp) and G.stats()["relax_launches"] > 1
+refuse(1 << 62)
+assert np.array_equal(G.batch_query(pairs, algo="bids"), exp) and G.stats()["relax_launches"] == 1
+""")
+
+
+def test_rounds_take_back_the_spill_area(tmp_path):
+    _run(tmp_path, ROADS + r"""
+assert np.array_equal(G.batch_query(pairs, algo="bids"), exp) and G.stats()["relax_launches"] == 1
+most(spill // 2)              # rounds need more than that, and less than the spill area
+G.set_option("resident", 0)
+G.set_option("queue_cap", 300000)
+for _ in range(2):
+    assert np.array_equal(G.batch_query(pairs, algo="bids"), exp)
+""")
