@@ -473,10 +473,14 @@ struct WaveOut {
 // Path lengths, then the paths of every pair slot of the wave's searches.
 int read_paths(ppsp_graph g, const RoundArgs &A, const PairDesc *pd, uint32_t npair, WaveOut &out) {
     hipStream_t st = g->st;
-    // room for the walks as they are found: 32 MB in all, at least 64 vertices each (longer ones are walked twice)
-    const uint32_t cap = (uint32_t)std::min<uint64_t>(g->n, std::max<uint64_t>(64, (4u << 20) / std::max(1u, npair)));
+    // room for the walks as they are found: 32 MB in all, at least 64 vertices each (longer ones are walked twice;
+    // all of them where the device has no such room)
+    uint32_t cap = (uint32_t)std::min<uint64_t>(g->n, std::max<uint64_t>(64, (4u << 20) / std::max(1u, npair)));
     CHK(ensure(g->pathlen, npair * 8ull));
-    CHK(ensure(g->pathvtx, npair * 8ull * cap));
+    if (ensure(g->pathvtx, npair * 8ull * cap) != PPSP_OK) {
+        g_last_error.clear();
+        cap = 0;
+    }
     CHK(ensure(g->pathoff, (npair + 1) * 8));
     HIPCHK(launch_path_walk(A, pd, g->pathlen.as<uint32_t>(), g->pathvtx.as<uint32_t>(), cap, st));
     std::vector<uint32_t> len(2 * (size_t)npair);

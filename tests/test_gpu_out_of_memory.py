@@ -129,3 +129,27 @@ G.set_option("queue_cap", 300000)
 for _ in range(2):
     assert np.array_equal(G.batch_query(pairs, algo="bids"), exp)
 """)
+
+
+def test_paths_without_room_for_the_walks(tmp_path):
+    """No room to keep the walks as they are found: each is walked again into its place."""
+    _run(tmp_path, r"""
+g = gen.lattice(64, 0.1, seed=9)
+pairs = np.random.default_rng(10).permutation(g.n)[:96].reshape(-1, 2).astype(np.uint32)
+exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+G = P.Graph.from_host(g)
+G.set_option("timeout_ms", 60000)
+for resident in (0, 1):
+    G.set_option("resident", resident)
+    assert np.array_equal(G.batch_query(pairs, algo="bids"), exp)
+    walks = 48 * 2 * g.n * 4
+    refuse(walks, walks + 1)
+    for algo in ("bids", "et"):
+        before = refused()
+        dist, (off, vtx) = G.batch_query(pairs, algo=algo, want_path=True)
+        assert refused() > before and np.array_equal(dist, exp)
+        for q in range(48):
+            assert oracle.check_path(g.n, g.row_ptr, g.col, g.w, vtx[off[q]:off[q + 1]], int(pairs[q, 0]),
+                                     int(pairs[q, 1]), int(exp[q])) == (0, 0), q
+    refuse(1 << 62)
+""")
