@@ -3067,7 +3067,8 @@ int ppsp_tune(ppsp_graph g, const uint32_t *pairs, uint32_t k, const ppsp_opts *
     CHK(check_opts(g, opts));
     auto &slot = g->tuned[opts->algo][opts->batch];
     char key[128];
-    snprintf(key, sizeof key, "ppsp-tune-v5 %016llx %u %u", (unsigned long long)g->fingerprint, opts->algo, opts->batch);
+    // v6: entries of before the resident searches hold launch shapes that keep a road graph in rounds
+    snprintf(key, sizeof key, "ppsp-tune-v6 %016llx %u %u", (unsigned long long)g->fingerprint, opts->algo, opts->batch);
     if (cache_path) {
         if (FILE *f = fopen(cache_path, "r")) {
             char line[256];
