@@ -2510,20 +2510,29 @@ uint64_t ppsp_heuristic_fx(int32_t x0, int32_t y0, int32_t x1, int32_t y1, uint3
 }
 
 // Whether the balls of a graph grow slowly, as on roads and grids: a search
-// from three vertices reaches 8,192 vertices only after 24 levels or more (or
-// never). There a query's frontier stays within a resident search's queues;
-// on a random graph of degree 8 (6 levels) it outgrows them after a few
-// rounds, which are then lost: 64 pairs took 1.46 ms against 0.85 in rounds.
+// from each of three vertices reaches 8,192 vertices only after 24 levels or
+// more. There a query's frontier stays within a resident search's queues; on a
+// random graph of degree 8 (6 levels) it outgrows them after a few rounds,
+// which are then lost: 64 pairs took 1.46 ms against 0.85 in rounds.
+//
+// A component of fewer vertices is small for any frontier and says nothing of
+// the others, so it is passed over: up to 64 roots are tried, from all over
+// the numbering (multiples of the golden ratio). Where none reaches 8,192
+// vertices, the queries are small ones: true.
 static bool ball_is_deep(uint32_t n, const uint64_t *row_ptr, const uint32_t *col) {
-    for (const uint64_t at : {(uint64_t)0, (uint64_t)n / 2, (uint64_t)n - 1}) {
-        uint32_t root = (uint32_t)at;
-        for (uint32_t k = 0; k < 64 && row_ptr[root + 1] == row_ptr[root]; k++) root = root + 1 < n ? root + 1 : 0;
+    std::unordered_map<uint32_t, uint32_t> passed;         // vertices of the small components
+    for (uint32_t k = 0, balls = 0; k < 64 && balls < 3; k++) {
+        uint32_t root = (uint32_t)((uint64_t)(k * 2654435769u) * n >> 32);
+        for (uint32_t j = 0; j < 64 && row_ptr[root + 1] == row_ptr[root]; j++) root = root + 1 < n ? root + 1 : 0;
+        if (passed.count(root)) continue;
         std::unordered_map<uint32_t, uint32_t> level{{root, 0}};
         std::vector<uint32_t> order{root};
         for (size_t h = 0; h < order.size() && order.size() < 8192; h++)
             for (uint64_t e = row_ptr[order[h]]; e < row_ptr[order[h] + 1]; e++)
                 if (level.emplace(col[e], level[order[h]] + 1).second) order.push_back(col[e]);
-        if (order.size() >= 8192 && level[order.back()] < 24) return false;
+        if (order.size() < 8192) passed.merge(level);
+        else if (level[order.back()] < 24) return false;
+        else balls++;
     }
     return true;
 }

@@ -195,3 +195,35 @@ def test_time_limit(P):
         assert e.code == P.E_TIMEOUT
     G.set_option("timeout_ms", 60000)
     assert np.array_equal(G.batch_query(pairs, algo="et"), exp)
+
+
+def _islands(g, isles, size, seed):
+    """g with `isles` paths of `size` vertices spread through its numbering, the first and the last number among them."""
+    n = g.n + isles * size
+    at = np.unique(np.linspace(0, n - 1, isles * size).astype(np.int64))
+    assert at.size == isles * size
+    land = np.setdiff1d(np.arange(n), at)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr.astype(np.int64)))
+    path = at.reshape(isles, size)
+    return gen.csr_from_edges(n, np.concatenate([land[src], path[:, :-1].ravel()]),
+                              np.concatenate([land[g.col], path[:, 1:].ravel()]),
+                              np.concatenate([g.w, np.full(isles * (size - 1), 7, g.w.dtype)])), land
+
+
+@pytest.mark.parametrize("isles,size", [(3, 1), (3, 7), (700, 2)])
+def test_small_components_do_not_decide(P, isles, size):
+    """Islands at the ends, in the middle and all over the numbering say nothing about the graph
+    beside them: a random one (its balls grow fast) goes in rounds at once, a grid stays resident."""
+    rng = np.random.default_rng(40)
+    n = 40000
+    fast = gen.csr_from_edges(n, np.repeat(np.arange(n), 4), rng.integers(0, n, 4 * n), rng.integers(1, 1000, 4 * n))
+    for base, resident in ((fast, False), (gen.grid(150, 200, 1, 1000, seed=41), True)):
+        g, land = _islands(base, isles, size, 42)
+        assert np.diff(g.row_ptr.astype(np.int64)).max() <= 64
+        pairs = land[gen.pairs_uniform(base.n, 40, seed=43)].astype(np.uint32)
+        exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+        G = _open(P, g)
+        for algo in ("bids", "et"):
+            assert np.array_equal(G.batch_query(pairs, algo=algo), exp)
+            launches = G.stats()["relax_launches"]
+            assert launches == 1 if resident else launches > 1 and launches % 16 == 0, (isles, size, algo, launches)
