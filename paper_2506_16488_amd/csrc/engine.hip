@@ -937,8 +937,9 @@ int resident_room(ppsp_graph g, const Plan &P) {
 }
 
 // Runs the wave as resident searches, in the buffers of resident_room; *redo
-// receives the queries whose frontier outgrew its queue (the round kernels run
-// those).
+// receives the queries whose frontier outgrew its queue, and those in which a
+// tentative distance passed 32 bits: keys beyond 32 bits have no order here, so
+// that may happen where none does in rounds. The round kernels run both.
 int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std::vector<uint32_t> &redo) {
     const uint32_t ns = (uint32_t)P.sd.size(), npair = (uint32_t)P.pairs.size(), per = P.pair2 ? 2 : 1, nq = ns / per;
     const uint64_t n = g->n;
@@ -1001,9 +1002,8 @@ int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std:
     out.mu.assign((uint64_t *)ho.data(), (uint64_t *)ho.data() + npair);
     const unsigned long long *qs = (const unsigned long long *)(ho.data() + o_stat);
     for (uint32_t q = 0; q < nq; q++, qs += RS_N) {
-        if (qs[RS_STATUS] & RES_OVERFLOW) return PPSP_E_OVERFLOW;
         if (qs[RS_STATUS] & RES_TIMEOUT) return PPSP_E_TIMEOUT;
-        if (qs[RS_STATUS] & RES_SPILL) redo.push_back(q);
+        if (qs[RS_STATUS] & (RES_SPILL | RES_OVERFLOW)) redo.push_back(q);
         out.stats[ST_ROUNDS] = std::max(out.stats[ST_ROUNDS], qs[RS_ROUNDS]);
         out.stats[ST_ENTRIES] += qs[RS_ENTRIES];
         out.stats[ST_SCANV] += qs[RS_SCANV];

@@ -14,7 +14,7 @@ enum ResidentStatus : uint32_t {
     RES_DONE = 0,       // answered
     RES_SPILL = 1,      // its frontier outgrew the queue: run it with the round kernels
     RES_TIMEOUT = 2,    // the time limit passed
-    RES_OVERFLOW = 4,   // a distance reached 2^32 - 1
+    RES_OVERFLOW = 4,   // a tentative distance reached 2^32 - 1: whether any does in order, the round kernels say
 };
 enum ResidentStat { RS_ROUNDS = 0, RS_ENTRIES = 1, RS_SCANV = 2, RS_SCANE = 3, RS_SUCC = 4, RS_CARRY = 5, RS_STATUS = 6, RS_N = 8 };
 

@@ -227,3 +227,33 @@ def test_small_components_do_not_decide(P, isles, size):
             assert np.array_equal(G.batch_query(pairs, algo=algo), exp)
             launches = G.stats()["relax_launches"]
             assert launches == 1 if resident else launches > 1 and launches % 16 == 0, (isles, size, algo, launches)
+
+
+def test_distances_near_the_limit(P):
+    """Keys beyond 32 bits lose their order in a resident search, so a tentative distance can
+    pass 2^32 where none does in rounds: an answer, not PPSP_E_OVERFLOW. Distances that do not
+    fit are an error either way."""
+    hops, tail = 30, 400
+    a, v, x = 1, 2, 3
+    chain = 4 + np.arange(hops)
+    end = 4 + hops + np.arange(tail)
+    src = [0, a, v] + [a, *chain] + list(end[:-1])
+    dst = [a, v, x] + [*chain, v] + list(end[1:])
+    w = [2147500000, 100000000, 2100000000] + [1000000] * (hops + 1) + [2000000] * (tail - 1)
+    g = gen.csr_from_edges(int(end[-1]) + 1, np.array(src), np.array(dst), np.array(w, np.uint32), symmetric=False)
+    G = _open(P, g)
+    pairs = np.array([[0, end[-1]], [0, v], [a, x]], np.uint32)
+    exp = [INF, 2147500000 + 31000000, 31000000 + 2100000000]
+    for resident in (0, 1):
+        G.set_option("resident", resident)
+        for k in (1, 3):
+            assert G.batch_query(pairs[:k], algo="bids", delta=1000000).tolist() == exp[:k], (resident, k)
+    w[2] = 4000000000
+    g = gen.csr_from_edges(int(end[-1]) + 1, np.array(src), np.array(dst), np.array(w, np.uint32), symmetric=False)
+    G = _open(P, g)
+    for resident in (0, 1):
+        G.set_option("resident", resident)
+        for algo in ("et", "sssp"):
+            with pytest.raises(P.PPSPError) as e:
+                G.batch_query(pairs[:1], algo=algo, delta=1000000)
+            assert e.value.code == P.E_OVERFLOW
