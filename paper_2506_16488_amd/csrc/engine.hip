@@ -981,7 +981,8 @@ int run_resident(ppsp_graph g, const Plan &P, bool want_path, WaveOut &out, std:
     R.mu = g->rout.as<uint64_t>();
     R.qstat = (unsigned long long *)(g->rout.as<char>() + o_stat);
     R.theta_mode = (uint32_t)g->opt_theta_mode;
-    R.ticks = (unsigned long long)g->opt_timeout_ms * g->clock_khz;
+    // a limit beyond 64 bits of ticks is the longest
+    R.ticks = (unsigned long long)std::min<unsigned __int128>((unsigned __int128)g->opt_timeout_ms * g->clock_khz, ~0ull);
     R.t_begin = (unsigned long long *)(g->rin.as<char>() + o_begin);
     // 1,024 threads a query: 256 pairs on the 256^2 grid take 1.36 ms (512 threads: 1.42), 64 BiD-A* pairs on the
     // 2048^2 lattice 29 ms (41), 1,000 of them 95 (109). Where queries queue for the compute units and are small,

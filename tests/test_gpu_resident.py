@@ -257,3 +257,28 @@ def test_distances_near_the_limit(P):
             with pytest.raises(P.PPSPError) as e:
                 G.batch_query(pairs[:1], algo=algo, delta=1000000)
             assert e.value.code == P.E_OVERFLOW
+
+
+def test_time_limit_is_kept(P):
+    """A search of many rounds, and a launch of many short ones, end with PPSP_E_TIMEOUT; the handle stays usable."""
+    g = gen.grid(300, 300, 1, 1000, seed=44)
+    pairs = np.array([[0, g.n - 1]], np.uint32)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    s = gen.grid(20, 20, 1, 1000, seed=45)
+    many = gen.pairs_uniform(s.n, 40000, seed=46, distinct=False)
+    for h, p, delta in ((g, pairs, 1), (s, many, 0)):
+        want = oracle.pp_batch(h.n, h.row_ptr, h.col, h.w, p[:500])
+        G = _open(P, h)
+        for algo in ("et", "sssp"):
+            G.set_option("timeout_ms", 1)
+            with pytest.raises(P.PPSPError) as e:
+                G.batch_query(p, algo=algo, delta=delta)
+            assert e.value.code == P.E_TIMEOUT
+            G.set_option("timeout_ms", 60000)
+            assert np.array_equal(G.batch_query(p[:500], algo=algo), want)
+            assert G.stats()["relax_launches"] == 1
+    # a limit whose clock ticks do not fit 64 bits is a long one (this one's product ends in 0.5 ms)
+    G = _open(P, g)
+    G.set_option("timeout_ms", 184467440737096)
+    assert np.array_equal(G.batch_query(pairs, algo="et", delta=1), exp)
+    assert G.stats()["relax_launches"] == 1
