@@ -2507,6 +2507,7 @@ uint64_t ppsp_heuristic_fx(int32_t x0, int32_t y0, int32_t x1, int32_t y1, uint3
     const unsigned __int128 d2 = (unsigned __int128)(dx * dx) + (unsigned __int128)(dy * dy);
     const unsigned __int128 q = d2 * ((unsigned __int128)w_scale * w_scale);
     if (q >> 63) return UINT64_MAX;
+    if (frac_bits > 31) return 0;                          // the root has at most 32 bits (and heur shifts by twice that)
     return heur(x0, y0, x1, y1, (uint64_t)w_scale * w_scale, frac_bits);
 }
 

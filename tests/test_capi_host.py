@@ -172,3 +172,11 @@ def test_binding_structs_match_the_header(tmp_path):
         assert int(got[cname]) == ctypes.sizeof(cls), cname
         for f, _ in cls._fields_:
             assert int(got["%s.%s" % (cname, f)]) == getattr(cls, f).offset, (cname, f)
+
+
+def test_heuristic_any_fraction():
+    """Every count of fractional bits, also those whose square passes 64 bits: from 32 on the value is 0."""
+    P = _ppsp()
+    c = (-123456, 77, 998877, -54321, 1000)
+    for fb in range(64):
+        assert P.heuristic_fx(*c, fb) == _h_exact(*c, fb), fb
