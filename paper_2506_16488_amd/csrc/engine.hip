@@ -894,6 +894,34 @@ uint32_t resident_spill(uint64_t n, uint64_t per) {
     return (uint32_t)std::min<uint64_t>(60000, std::max({small, share, n / 256}));
 }
 
+// Where few queries on a large graph leave the chip to the round kernels, which
+// put every unit on one query and with a heuristic advance several hops a
+// round. The rounds a query needs grow with the root of n and the arcs of each
+// with a = m / sqrt(n); a unit takes 400 of them a microsecond, a round of the
+// chip about 17 however many they are, so a decides, the same at all sizes: a
+// wave of nq queries goes in rounds if nq < (a - from) / per. And a query whose
+// frontier outgrows its spill area is lost time: in rounds where a is beyond
+// `spill` entries for each of the area. Resident / rounds on neighbourhood
+// graphs of 4 to 16 arcs a vertex, corner to corner and uniform pairs:
+//   a (n, degree)         BiDS x1, x4, x16, x64    ET x1, x4    BiD-A* x1, x16, x64, x256    A* x1, x16, x256
+//   4,096 (2^18, 8)       .48  .44  .29  .24       .33  .29     1.06  .90  .67  .53          .81  .69  .39
+//   4,096 (2^20, 4)       .52  .49  .31  .26       .35  .28      .83  .71  .59  .44          .66  .58  .40
+//   8,192 (2^18, 16)      .86  .76  .48  .41       .59  .49     1.85 1.56 1.00  .76         1.10  .94  .37
+//   8,192 (2^22, 4)       .82  .81  .53  .37       .58  .44     1.35 1.21  .92  .60         1.07 1.03  .51
+//   12,288 (2^20, 12)    1.12 1.03  .57  .48       .79  .60     2.16 1.70  .91  .77         1.35 1.11  .47
+//   16,384 (2^22, 8)     1.37 1.36  .73  .59      1.09  .83     2.95 2.58 1.48 1.17         2.39 2.12  .82
+//   16,384 (2^24, 4)     1.75 1.46  .88  .63      1.23  .82     3.03 2.19 1.57  .91         2.27 1.76  .76
+//   24,576 (2^22, 12)    2.20 2.03 1.04 1.27      1.54 1.21     2.70 2.15 1.70 1.43         2.05 1.82 1.48
+//   32,768 (2^22, 16)    3.37 3.16 1.96 1.80      1.87 1.49     1.83 1.56 1.34 1.24         1.60 1.47 1.33
+bool rounds_do_more(uint64_t n, uint64_t m, uint64_t nq, bool pair, bool heur) {
+    struct { double from, per, spill; } r = {15000, 1000, 2.0};          // SSSP, ET
+    if (pair) r = {10500, 500, 1.45};                                    // BiDS
+    if (heur) r = {7000, 100, 1.2};                                      // A*
+    if (pair && heur) r = {4800, 80, 0.85};                              // BiD-A*
+    const double a = (double)m / std::sqrt((double)n);
+    return (double)nq < (a - r.from) / r.per || a > r.spill * resident_spill(n, pair ? 2 : 1);
+}
+
 // Whether the wave runs as resident searches, one workgroup per query
 // (resident.hip): independent queries (bidirectional pairs, or searches
 // without partner copies) on a graph of small degrees whose frontiers stay
@@ -907,18 +935,11 @@ bool resident_ok(ppsp_graph g, const Plan &P) {
         g->opt_local != 16 || g->opt_local_plain || g->opt_local_fill || g->opt_min_chunk != 16 ||
         g->opt_local_small != 4 || g->opt_local_pct != 90 || g->opt_defer_pct != 105)
         return false;
-    // A few queries on a large graph leave the chip to the round kernels,
-    // which put every unit on one query and with a heuristic advance several
-    // hops a round. Measured on corner-to-corner pairs, resident / rounds in
-    // ms: BiD-A* on 2048^2 (n = 2^22) x1 42 / 23, x4 42 / 32, x16 45 / 53,
-    // on 1024^2 x1 about 3 / 4; BiDS on 2048^2 x1 37 / 43, x4 38 / 63, on
-    // 4096^2 x1 193 / 104, x8 175 / 199; all distances on 2048^2 48 / 79.
     const uint64_t nq = P.sd.size() / (P.pair2 ? 2 : 1), n = g->n;
     const uint64_t per = P.pair2 ? 2 : 1;
     const uint64_t areas = 64ull * resident_spill(n, per);
     if (areas > per * n * 4 && nq * (per * n * 4 + areas) > std::max<uint64_t>(state_budget(g), 16 * n)) return false;
-    const bool heur = is_astar_kind(P.sd[0].kind);
-    if (heur ? n > 3ull << 19 && nq < n >> 18 : n > 1ull << 22 && nq < n >> 21) return false;
+    if (rounds_do_more(n, g->m, nq, P.pair2, is_astar_kind(P.sd[0].kind))) return false;
     if (P.pair2) return P.G == 2 && P.pairs.size() * 2 == P.sd.size();
     if (P.G != 1) return false;
     for (const SearchDesc &d : P.sd) {

@@ -282,3 +282,36 @@ def test_time_limit_is_kept(P):
     G.set_option("timeout_ms", 184467440737096)
     assert np.array_equal(G.batch_query(pairs, algo="et", delta=1), exp)
     assert G.stats()["relax_launches"] == 1
+
+
+def _neighbours(side, seed):
+    """A jittered lattice of `side` x `side` with 16 neighbours a vertex and coordinates."""
+    rng = np.random.default_rng(seed)
+    ids = np.arange(side * side).reshape(side, side)
+    xy = np.stack([ids % side, ids // side], -1).reshape(-1, 2) * 256 + rng.integers(0, 256, (side * side, 2))
+    a, b = [], []
+    for dr, dc in ((0, 1), (1, 0), (1, 1), (1, -1), (0, 2), (2, 0), (1, 2), (2, -1)):
+        a.append(ids[:side - dr, max(0, -dc):side - max(0, dc)].ravel())
+        b.append(ids[dr:, max(0, dc):side + min(0, dc)].ravel())
+    a, b = np.concatenate(a), np.concatenate(b)
+    w = np.ceil(1000 * np.sqrt(((xy[a] - xy[b]) ** 2).sum(1)) / 256 * rng.uniform(1, 1.3, a.size)).astype(np.int64) + 1
+    return gen.csr_from_edges(side * side, a, b, w, coords=xy.astype(np.int32))
+
+
+@pytest.mark.parametrize("side,algo,few,many", [(340, "bidastar", 4, 16), (340, "astar", 0, 1), (340, "bids", 0, 1),
+                                                (640, "bidastar", 24, 72), (640, "astar", 16, 40), (700, "bids", 1, 4)])
+def test_few_queries_on_many_arcs(P, side, algo, few, many):
+    """The arcs of a round decide from how many queries on a unit each does more than the whole chip on all of them."""
+    g = _neighbours(side, side)
+    pairs = gen.pairs_uniform(g.n, many, seed=50)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs[:4])
+    G = _open(P, g, reorder=True)
+    for k, resident in ((few, False), (many, True)):
+        if k:
+            d = G.batch_query(pairs[:k], algo=algo)
+            launches = G.stats()["relax_launches"]
+            assert launches == 1 if resident else launches % 16 == 0, (k, launches)
+            assert np.array_equal(d[:4], exp[:k])
+            G.set_option("resident", 0)
+            assert np.array_equal(G.batch_query(pairs[:k], algo=algo), d)
+            G.set_option("resident", 1)
