@@ -5,8 +5,8 @@
 // the rounds themselves: two launches each, and in each a chain of dependent
 // accesses to lines that any XCD may have written. Here a query lives on one
 // compute unit:
-//   - its rounds are separated by one workgroup barrier instead of two
-//     kernel boundaries;
+//   - a round takes three workgroup barriers (three more for each further
+//     batch of candidates) instead of two kernel boundaries;
 //   - its distance words are only ever touched by that workgroup, so plain
 //     loads and stores serve, and the words stay in one XCD's L2;
 //   - its frontier (two queues by round parity) is in LDS, with a spill area
@@ -16,7 +16,7 @@
 // 0.66, 64 on it 7.7 / 1.35, 256 BiD-A* on a 2048^2 lattice 69.8 / 44.8, 100
 // A* on an 800 x 600 one 22.6 / 10.6, 48 BiDS on a directed one 24.4 / 6.9,
 // all distances on 1024^2 27.2 / 13.0. What bounds a query: its rounds, one
-// after the other, about 5 us each when small (a chain of two barriers, three
+// after the other, about 5 us each when small (a chain of three barriers, three
 // dependent accesses to memory and the LDS lists between), and 400 to 470
 // arcs a microsecond on one compute unit beyond; a batch lasts as long as its
 // longest query.
@@ -126,8 +126,10 @@ struct __attribute__((aligned(16))) FarList { uint32_t n, mk0, mk1, pad; };
 
 }  // namespace
 
-// B threads a query. LDS for 1024: 36 KB queues, 12 KB candidates, 20 KB bids,
-// 64 KB bid tables; for 512 half of it, so that two workgroups share a CU.
+// B threads a query. LDS for 1,024 with a heuristic: 30 KB queues and keys,
+// 8 KB candidates, 21 KB extracted entries and owners of arcs, 32 KB bids, 64 KB
+// bid tables, in all 155.2 of a unit's 160; for 512 half of it, so that two
+// workgroups share a unit.
 template <int B, bool PAIR, bool HEUR, bool REV>
 __global__ __launch_bounds__(B) void k_resident(ResidentArgs A) {
     constexpr uint32_t KIND = PAIR ? (HEUR ? K_BIDA_F : K_2DIST) : (HEUR ? K_ASTAR : K_DIST);
@@ -148,6 +150,9 @@ __global__ __launch_bounds__(B) void k_resident(ResidentArgs A) {
     __shared__ FarList s_far[2];
     __shared__ uint32_t s_nbid, s_err;
     __shared__ unsigned long long s_stat[RS_N];
+    static_assert(sizeof(lq) + sizeof(lk) + sizeof(s_idx) + sizeof(s_ext) + sizeof(s_owner) + sizeof(s_bid) +
+                  sizeof(s_tab) + sizeof(s_hand) + sizeof(s_far) + sizeof(s_nbid) + sizeof(s_err) + sizeof(s_stat) <=
+                  160 * B, "a unit's 160 KB hold one workgroup of 1,024 threads or two of 512");
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid / 64), q = blockIdx.x;
     const SearchDesc sd = A.sd[PAIR ? 2 * q : q];
