@@ -1,6 +1,7 @@
 """Builds the gfx950 HIP libraries in-tree with hipcc: libppsp.so (the
 search library behind include/ppsp.h) and libppsp_probe.so (the benchmark's
-scattered-access probe, outside the search library's interface)."""
+scattered-access probe and the integer root's, outside the search library's
+interface)."""
 from __future__ import annotations
 
 import os
@@ -13,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 SO = os.path.join(HERE, "libppsp.so")
 SOURCES = ["engine.hip", "kernels.hip", "resident.hip", "mlp.hip"]
 PROBE_SO = os.path.join(HERE, "libppsp_probe.so")
-PROBE_SOURCES = ["randbench.hip"]
+PROBE_SOURCES = ["randbench.hip", "rootprobe.hip"]
 ARCH = "gfx950"
 
 
