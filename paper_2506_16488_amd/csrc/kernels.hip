@@ -947,7 +947,8 @@ __device__ __forceinline__ void relax_piece(const RoundArgs &A, WaveStage &st, u
 // the words of the hubs of one pair stay in a die's L2 while it works on that
 // pair alone. 128 queries on R-MAT 22: rounds of the longest lists 7.7 ms
 // before, 5.0 in bins, the batch 408 / 342. A short list (in parts) is dealt
-// out within each die: with claims a round of 0.18 ms took 0.34.
+// out to workgroups split by the dies' records (die_share): with claims a round
+// of 0.18 ms took 0.34.
 template <bool MEMO, bool REV, bool BINS>
 __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
     __shared__ WaveStage st;
@@ -960,10 +961,12 @@ __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
     uint32_t *qcout = &A.qcount[np * NSEG + sego];
     unsigned long long c_succ = 0;
     uint64_t nh = 0;
+    uint32_t recs[XCDS];                                    // of each die's bins
     if (BINS) {
-        uint32_t mine = 0;
+        uint32_t mine = 0;                                  // this lane's bins are die lane % XCDS's
         for (uint32_t b = lane_id(); b < A.hbins; b += WAVE) mine += hbin_size(A, b);
-        nh = wave_sum_u64(mine);
+        for (int o = XCDS; o < WAVE; o <<= 1) mine += __shfl_xor(mine, o);
+        for (uint32_t y = 0; y < XCDS; y++) nh += recs[y] = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)y);
     } else {
         nh = min((uint64_t)*A.hcount, (uint64_t)A.hcap);
     }
@@ -978,35 +981,35 @@ __global__ __launch_bounds__(WAVE, 5) void k_heavy(RoundArgs A) {
             relax_piece<MEMO, REV>(A, st, scnt, h1.x, h1.z, b, min(ee, b + len), np, stamp, qout, qcout, count, &c_succ);
     };
     if (BINS) {
-        // this die's bins, then (of a long list) those of the next
+        // a long list: this die's bins, then those of the next
+        const DieShare share = die_share(recs, gridDim.x, blockIdx.x);
         for (uint32_t v = 0; v < XCDS; v++) {
-            const uint32_t x = (blockIdx.x + v) % XCDS, own = x + XCDS * lane_id();
+            const uint32_t x = parts > 1 ? share.x : (blockIdx.x + v) % XCDS, own = x + XCDS * lane_id();
             // lane l: the records of the die's bins up to its l-th (HBINS / XCDS of them at most)
             uint32_t upto = own < A.hbins ? hbin_size(A, own) : 0;
             for (int o = 1; o < WAVE; o <<= 1) {
                 const uint32_t y = __shfl_up(upto, o);
                 if (lane_id() >= (uint32_t)o) upto += y;
             }
-            const uint32_t recs = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1), pieces = recs * parts;
-            // pieces k, k + step .. below end: dealt out (a short list) among the
-            // workgroups that the die has, at least one (the host keeps one list
-            // for a grid below XCDS), or hclaim records claimed from the die's
-            // counter
-            uint32_t k = blockIdx.x / XCDS, end = pieces, step = die_blocks(gridDim.x, x);
+            const uint32_t many = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1), pieces = many * parts;
+            // pieces k, k + step .. below end: dealt out (a short list; the host
+            // keeps one list for a grid below XCDS), or hclaim records claimed
+            // from the die's counter
+            uint32_t k = share.first, end = pieces, step = share.step;
             do {
                 if (parts == 1) {
                     unsigned long long got = 0;
-                    if (lane_id() == 0 && recs) got = atomicAdd(A.hcount + hbin_claim(x), (unsigned long long)A.hclaim);
-                    k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)recs));
-                    end = min(k + A.hclaim, recs);
+                    if (lane_id() == 0 && many) got = atomicAdd(A.hcount + hbin_claim(x), (unsigned long long)A.hclaim);
+                    k = __builtin_amdgcn_readfirstlane((uint32_t)min(got, (unsigned long long)many));
+                    end = min(k + A.hclaim, many);
                     step = 1;
                 }
                 for (; k < end; k += step) {
-                    const uint32_t rec = k % recs, l = (uint32_t)__popcll(__ballot(upto <= rec));
+                    const uint32_t rec = k % many, l = (uint32_t)__popcll(__ballot(upto <= rec));
                     const uint32_t before = l ? (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)l - 1) : 0u;
-                    piece((uint64_t)(x + XCDS * l) * A.hbcap + (rec - before), k / recs);
+                    piece((uint64_t)(x + XCDS * l) * A.hbcap + (rec - before), k / many);
                 }
-            } while (parts == 1 && end < recs);
+            } while (parts == 1 && end < many);
             if (parts > 1) break;
         }
     } else {

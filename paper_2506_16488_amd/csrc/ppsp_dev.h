@@ -78,10 +78,39 @@ constexpr uint32_t HBINS = 256;                // most bins of the hub list (Rou
 __host__ __device__ constexpr uint32_t hbin_count(uint32_t b) { return 8 * (1 + b); }
 __host__ __device__ constexpr uint32_t hbin_claim(uint32_t x) { return 8 * (1 + HBINS + x); }
 constexpr uint32_t HCOUNT_WORDS = 8 * (1 + HBINS + XCDS);
-// Workgroups of die x in a grid of `grid` (workgroup b is on die b % XCDS): not
-// the same for every die unless the grid is a multiple of XCDS. Workgroup b is
-// number b / XCDS of its die, and takes every die_blocks-th piece from there.
-__host__ __device__ constexpr uint32_t die_blocks(uint32_t grid, uint32_t x) { return (grid + XCDS - 1 - x) / XCDS; }
+// Which pieces of a short list in bins a workgroup of the hub-list kernel takes:
+// first, first + step, ... of die x's. The workgroups (workgroup b is on die b %
+// XCDS), die after die, are split in proportion to the dies' records, at least
+// one for each die that has any; the grid is at least XCDS. While all dies hold
+// the same a workgroup takes its own die's. A split by die alone leaves the chip
+// to one die when one pair is left: 16 BiDS queries on R-MAT 20, 15 of them
+// between isolated vertices, 14.9 ms (6.4 in proportion; 9.0 from one list in
+// whole records), 16 real ones on R-MAT 22 at the tuned step 75 (61). Only beyond
+// 1.25, 1.5 or 2 times the mean: the same.
+struct DieShare { uint32_t x, first, step; };
+__host__ __device__ inline DieShare die_share(const uint32_t (&recs)[XCDS], uint32_t grid, uint32_t b) {
+    uint32_t total = 0, some = 0;
+    for (uint32_t y = 0; y < XCDS; y++) {
+        total += recs[y];
+        some += recs[y] != 0;
+    }
+    const uint32_t own = b % XCDS, odd = grid % XCDS;
+    const uint32_t rank = own * (grid / XCDS) + (own < odd ? own : odd) + b / XCDS;   // die after die
+    const float each = (float)(grid - some) / (float)total;
+    DieShare r = {0, 0, 1};
+    uint32_t before = 0, dies = 0, begin = 0;
+    for (uint32_t y = 0; y < XCDS; y++) {
+        if (recs[y] == 0) continue;
+        before += recs[y];
+        dies++;
+        const uint32_t most = grid - (some - dies);            // the dies after it keep one each
+        uint32_t end = (uint32_t)(each * (float)before + 0.5f) + dies;
+        end = dies == some || end > most ? most : end;
+        if (begin <= rank && rank < end) r = {y, rank - begin, end - begin};
+        begin = end;
+    }
+    return r;
+}
 constexpr uint32_t HEAVY_CHUNK = 2048;         // arcs per heavy-list chunk
 constexpr int NSEG = 64;                       // append segments of a frontier queue
 

@@ -111,3 +111,25 @@ def test_hub_bins_of_uneven_pairs(P):
     for _ in range(2):
         assert np.array_equal(G.batch_query(pairs, algo="sssp", delta=1 << 20), exp)
         assert G.stats()["retries"] == 0 and G.stats()["heavy_chunks"] > 0
+
+
+@pytest.mark.parametrize("real", [1, 2, 5])
+def test_hub_bins_of_few_pairs(P, real):
+    """Most pairs end at once, so the list lies in the bins of a few dies, at changing places."""
+    g = _hubs(9)
+    n = g.n + 200
+    rp = np.concatenate([g.row_ptr, np.full(200, g.row_ptr[-1], g.row_ptr.dtype)])
+    idle = g.n + np.arange(200).reshape(-1, 2)
+    G = P.Graph(n, rp, g.col, g.w, symmetric=True)
+    G.set_option("timeout_ms", 60000)
+    for k, at in ((16, 0), (16, 9), (40, 30), (100, 93)):
+        pairs = idle[:k].copy()
+        pairs[at:at + real] = gen.pairs_uniform(g.n, real, seed=70 + real)
+        pairs = pairs.astype(np.uint32)
+        exp = oracle.pp_batch(n, rp, g.col, g.w, pairs)
+        for waves, grid in ((24, 0), (0, 20)):
+            G.set_option("heavy_waves", waves)
+            G.set_option("grid_blocks", grid)
+            for algo in ("bids", "et"):
+                assert np.array_equal(G.batch_query(pairs, algo=algo), exp), (k, at, waves, algo)
+    assert G.stats()["heavy_arcs"] > 0
