@@ -913,13 +913,23 @@ uint32_t resident_spill(uint64_t n, uint64_t per) {
 //   16,384 (2^24, 4)     1.75 1.46  .88  .63      1.23  .82     3.03 2.19 1.57  .91         2.27 1.76  .76
 //   24,576 (2^22, 12)    2.20 2.03 1.04 1.27      1.54 1.21     2.70 2.15 1.70 1.43         2.05 1.82 1.48
 //   32,768 (2^22, 16)    3.37 3.16 1.96 1.80      1.87 1.49     1.83 1.56 1.34 1.24         1.60 1.47 1.33
-bool rounds_do_more(uint64_t n, uint64_t m, uint64_t nq, bool pair, bool heur) {
+// A wider step has fewer rounds of more arcs (and vertices that are lowered
+// again): with `step` = Delta over its default, a grows as below, without a
+// heuristic only from 4 times the default on. At a = 4,096 (2^20, 4) / 8,192
+// (2^22, 4), steps of 1, 4, 16, 64, 256: BiDS x1 .52 .50 .61 1.83 2.46 / .82 .78
+// 1.22 1.78 1.55; all distances .37 .39 .47 .70 1.29 / .58 .60 .71 1.93 1.67;
+// BiD-A* x64 .62 1.00 1.10 2.01 1.80 / .97 1.59 2.90 1.59 1.35; A* x1 at 4,096 .66
+// 1.12 1.26 1.30 3.1.
+bool rounds_do_more(uint64_t n, uint64_t m, uint64_t nq, bool pair, bool heur, double step) {
     struct { double from, per, spill; } r = {15000, 1000, 2.0};          // SSSP, ET
     if (pair) r = {10500, 500, 1.45};                                    // BiDS
     if (heur) r = {7000, 100, 1.2};                                      // A*
     if (pair && heur) r = {4800, 80, 0.85};                              // BiD-A*
-    const double a = (double)m / std::sqrt((double)n);
-    return (double)nq < (a - r.from) / r.per || a > r.spill * resident_spill(n, pair ? 2 : 1);
+    const double a = (double)m / std::sqrt((double)n), s = std::min(std::max(step, 1.0 / 16), 256.0);
+    const double round = a * (heur ? std::pow(std::min(s, 64.0), pair ? 0.4 : 0.25)
+                                   : std::pow(std::min(std::max(s / 4, 1.0), 16.0), 0.45));
+    const double front = a * std::pow(std::max(s, 1.0), 0.4);
+    return (double)nq < (round - r.from) / r.per || front > r.spill * resident_spill(n, pair ? 2 : 1);
 }
 
 // Whether the wave runs as resident searches, one workgroup per query
@@ -939,7 +949,9 @@ bool resident_ok(ppsp_graph g, const Plan &P) {
     const uint64_t per = P.pair2 ? 2 : 1;
     const uint64_t areas = 64ull * resident_spill(n, per);
     if (areas > per * n * 4 && nq * (per * n * 4 + areas) > std::max<uint64_t>(state_budget(g), 16 * n)) return false;
-    if (rounds_do_more(n, g->m, nq, P.pair2, is_astar_kind(P.sd[0].kind))) return false;
+    // key units are doubled for pairs; the default step is twice the mean weight
+    const double step = g->opt_theta_mode == 3 ? 256.0 : (double)P.delta[0] / (double)(per * 2 * g->wmean);
+    if (rounds_do_more(n, g->m, nq, P.pair2, is_astar_kind(P.sd[0].kind), step)) return false;
     if (P.pair2) return P.G == 2 && P.pairs.size() * 2 == P.sd.size();
     if (P.G != 1) return false;
     for (const SearchDesc &d : P.sd) {

@@ -315,3 +315,19 @@ def test_few_queries_on_many_arcs(P, side, algo, few, many):
             G.set_option("resident", 0)
             assert np.array_equal(G.batch_query(pairs[:k], algo=algo), d)
             G.set_option("resident", 1)
+
+
+def test_wide_steps_go_in_rounds(P):
+    """The step decides too: a wide one has rounds of many arcs and a large frontier, a narrow one small rounds."""
+    g = _neighbours(640, 51)
+    pairs = gen.pairs_uniform(g.n, 4, seed=52)
+    exp = oracle.pp_batch(g.n, g.row_ptr, g.col, g.w, pairs)
+    G = _open(P, g, reorder=True)
+    d = G.get_option("default_delta")
+    for algo, mode, delta, resident in (("bids", 2, 0, True), ("bids", 2, 64 * d, False), ("bids", 3, 0, False),
+                                        ("sssp", 2, 4 * d, True), ("sssp", 2, 256 * d, False),
+                                        ("bidastar", 2, d, False), ("bidastar", 2, d // 8, True)):
+        G.set_option("theta_mode", mode)
+        assert np.array_equal(G.batch_query(pairs, algo=algo, delta=delta), exp), (algo, mode, delta)
+        launches = G.stats()["relax_launches"]
+        assert launches == 1 if resident else launches % 16 == 0, (algo, mode, delta, launches)
