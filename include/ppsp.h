@@ -552,7 +552,8 @@ int ppsp_last_stats(ppsp_graph g, ppsp_stats *stats);
  *   "use_graph"       1: replay rounds through a captured hipGraph
  *   "resident"        1 (default): independent queries on graphs of small degree (roads, grids)
  *                     run one workgroup per query, from its roots to its end, where that is the
- *                     faster way and no option that shapes rounds is set; 0: always in rounds
+ *                     faster way (by the arcs of a round, the queries and the step) and no option
+ *                     that shapes or times rounds is set; 0: always in rounds
  *   "timeout_ms"      limit on one wave (0 = none): of its round loop, by the host's clock every
  *                     "rounds_per_sync" rounds, and of its resident launch, by the device's
  *                     clock every round of a query

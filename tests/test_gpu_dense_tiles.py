@@ -1,6 +1,6 @@
 """Dense bitmaps are read in tiles of runs from all over them: sizes around a
-word, a run (1,024 vertices), a tile (2,048) and several, with one and with
-many dense searches, against the oracle."""
+word, a run (512 vertices), two runs, a tile (2,048) and several, with one and
+with many dense searches, against the oracle."""
 import numpy as np
 import pytest
 
