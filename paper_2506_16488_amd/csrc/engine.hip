@@ -913,6 +913,9 @@ uint32_t resident_spill(uint64_t n, uint64_t per) {
 //   16,384 (2^24, 4)     1.75 1.46  .88  .63      1.23  .82     3.03 2.19 1.57  .91         2.27 1.76  .76
 //   24,576 (2^22, 12)    2.20 2.03 1.04 1.27      1.54 1.21     2.70 2.15 1.70 1.43         2.05 1.82 1.48
 //   32,768 (2^22, 16)    3.37 3.16 1.96 1.80      1.87 1.49     1.83 1.56 1.34 1.24         1.60 1.47 1.33
+// and uniform pairs alone on road lattices, BiD-A* x1, x8, x32 and A* x1, x8 at a
+// = 5,930 .99 1.03 .91, .84 .79 (1448^2: .81 .93 .78, .71 .69), at 7,375 .94 1.17
+// 1.09, .76 .76, at 8,390 1.15 1.34 1.11, .89 .84.
 // A wider step has fewer rounds of more arcs (and vertices that are lowered
 // again): with `step` = Delta over its default, a grows as below, without a
 // heuristic only from 4 times the default on. At a = 4,096 (2^20, 4) / 8,192
@@ -923,8 +926,8 @@ uint32_t resident_spill(uint64_t n, uint64_t per) {
 bool rounds_do_more(uint64_t n, uint64_t m, uint64_t nq, bool pair, bool heur, double step) {
     struct { double from, per, spill; } r = {15000, 1000, 2.0};          // SSSP, ET
     if (pair) r = {10500, 500, 1.45};                                    // BiDS
-    if (heur) r = {7000, 100, 1.2};                                      // A*
-    if (pair && heur) r = {4800, 80, 0.85};                              // BiD-A*
+    if (heur) r = {8000, 100, 1.2};                                      // A*
+    if (pair && heur) r = {5600, 70, 0.85};                              // BiD-A*
     const double a = (double)m / std::sqrt((double)n), s = std::min(std::max(step, 1.0 / 16), 256.0);
     const double round = a * (heur ? std::pow(std::min(s, 64.0), pair ? 0.4 : 0.25)
                                    : std::pow(std::min(std::max(s / 4, 1.0), 16.0), 0.45));

@@ -298,7 +298,7 @@ def _neighbours(side, seed):
     return gen.csr_from_edges(side * side, a, b, w, coords=xy.astype(np.int32))
 
 
-@pytest.mark.parametrize("side,algo,few,many", [(340, "bidastar", 4, 16), (340, "astar", 0, 1), (340, "bids", 0, 1),
+@pytest.mark.parametrize("side,algo,few,many", [(400, "bidastar", 4, 16), (400, "astar", 0, 1), (400, "bids", 0, 1),
                                                 (640, "bidastar", 24, 72), (640, "astar", 16, 40), (700, "bids", 1, 4)])
 def test_few_queries_on_many_arcs(P, side, algo, few, many):
     """The arcs of a round decide from how many queries on a unit each does more than the whole chip on all of them."""
