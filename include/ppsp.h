@@ -556,7 +556,7 @@ int ppsp_last_stats(ppsp_graph g, ppsp_stats *stats);
  *                     that shapes or times rounds is set; 0: always in rounds
  *   "timeout_ms"      limit on one wave (0 = none): of its round loop, by the host's clock every
  *                     "rounds_per_sync" rounds, and of its resident launch, by the device's
- *                     clock every round of a query
+ *                     clock in the first and every eighth round of a query
  *   "queue_cap"       frontier queue capacity in entries (grows x4, with a rerun of
  *                     the wave, whenever a round overflows it)
  *   "heavy_cap"       heavy-list capacity in arc chunks (grows the same way)

@@ -232,8 +232,9 @@ __global__ __launch_bounds__(B) void k_resident(ResidentArgs A) {
         if (tid == 0) {
             s_hand[rst] = {0, 0, NO_KEY, NO_KEY, INF64, 0, 0};
             s_nbid = 0;
-            // every round: a launch of many short queries has no others
-            if (A.ticks && wall_clock64() - t_begin > A.ticks) s_hand[nxt].stop = 1;
+            // from the first round on: a launch of many short queries has few others (every round: single queries
+            // and all distances of a source 1 to 1.5% slower)
+            if (A.ticks && (r & 7) == 0 && wall_clock64() - t_begin > A.ticks) s_hand[nxt].stop = 1;
         }
         // Liveness, termination and bound (Table 2; a side that ran dry while
         // nothing could be pruned has covered its component, Appendix B), and

@@ -62,7 +62,8 @@ def _run(tmp_path, body):
     subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", str(c), "-o", str(so)])
     py.write_text(PRELUDE + body + "\nprint('case done', flush=True)\n")
     r = subprocess.run([sys.executable, str(py), str(so)], cwd=ROOT, capture_output=True, text=True, timeout=100,
-                       env=dict(os.environ, PYTHONPATH=ROOT))
+                       env=dict(os.environ, PYTHONPATH=os.pathsep.join(
+                           [ROOT] + os.environ.get("PYTHONPATH", "").split(os.pathsep)).rstrip(os.pathsep)))
     assert r.returncode == 0 and "case done" in r.stdout, r.stdout[-1000:] + r.stderr[-2000:]
 
 
